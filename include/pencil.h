@@ -109,8 +109,10 @@ typedef struct {
      * 1 loads them directly (both ciphertext components per wave), 2 loads
      * them directly for one component per wave.  v mod 3 is the workgroup's
      * chunk: 4 x 8, 2 x 16 or 8 x 4 rows (kinds 0 and 1), 4 x 4, 2 x 8 or 8 x 2
-     * (kind 2).  Results do not depend on it; pencil_plan_auto picks a kind-1
-     * chunk by a cost model, pencil_autotune by measurement. */
+     * (kind 2).  Products with many outputs per slot and a long contraction run
+     * on the matrix cores instead, whatever the schedule.  Results do not depend
+     * on it; pencil_plan_auto picks a kind-1 chunk by a cost model,
+     * pencil_autotune by measurement. */
     int32_t sched[3];
 } pencil_plan;
 

@@ -25,6 +25,55 @@ typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint64_t split30(uint64_t v) { return (v & 0x3FFFFFFFull) | ((v >> 30) << 32); }
 __device__ __forceinline__ uint64_t unsplit30(uint64_t s) { return (s & 0xFFFFFFFFull) | ((s >> 32) << 30); }
 
+// A wave-uniform 64-bit pointer, kept in scalar registers.
+__device__ __forceinline__ const char* uni(const char* p) {
+  const uint64_t v = (uint64_t)p;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return (const char*)(((uint64_t)hi << 32) | lo);
+}
+
+// Digits of a residue v < 2^60 for the matrix-core multiply-accumulate: the
+// bytes of v + 0x80..80 with their top bits flipped are the two's complement
+// digits d_i of v = sum d_i 2^(8 i), -128 <= d_i < 128.
+__device__ __forceinline__ uint64_t digits8(uint64_t v) {
+  return (v + 0x8080808080808080ull) ^ 0x8080808080808080ull;
+}
+
+// Forms in which the forward transforms store a polynomial (tile j of `count`,
+// limb l): plain residues, split residues, or for the matrix-core
+// multiply-accumulate slot-blocked [l][slot group][j][kMxGroup slots] digits,
+// digits with their bytes reversed, or split residues.
+__device__ __forceinline__ uint64_t form_value(uint64_t v, int form) {
+  switch (form) {
+    case FORM_PLAIN: return v;
+    case FORM_DIGITS: return digits8(v);
+    case FORM_REVERSED: {
+      const uint64_t d = digits8(v);
+      return (uint64_t)__builtin_bswap32((uint32_t)d) << 32 | __builtin_bswap32((uint32_t)(d >> 32));
+    }
+    default: return split30(v);
+  }
+}
+__device__ __forceinline__ bool form_blocked(int form) { return form >= FORM_DIGITS; }
+
+// Store f(slot) for every slot of a polynomial in 16-byte pairs (f returns the
+// stored word of a slot).
+template <int LOGN, typename F>
+__device__ __forceinline__ void store_form(uint64_t* dst, int form, int64_t count, int L, int l, int64_t j, F f) {
+  constexpr int n = 1 << LOGN;
+  if (!form_blocked(form)) {
+    PENCIL_GLOBAL u64x2* o2 = (PENCIL_GLOBAL u64x2*)gview(dst + (j * L + l) * n);
+    for (int i = threadIdx.x; i < n / 2; i += blockDim.x) o2[i] = u64x2{f(2 * i), f(2 * i + 1)};
+    return;
+  }
+  PENCIL_GLOBAL uint64_t* o = gview(dst + ((int64_t)l * (n / kMxGroup) * count + j) * kMxGroup);
+  const int64_t group = count * kMxGroup;
+  for (int i = threadIdx.x; i < n / 2; i += blockDim.x) {
+    const int s = 2 * i;
+    *(PENCIL_GLOBAL u64x2*)(o + (s / kMxGroup) * group + s % kMxGroup) = u64x2{f(s), f(s + 1)};
+  }
+}
+
 // ---------------------------------------------------------- encode helpers
 // round(q m / t) mod q_l for m in [0, t): Delta * m + round(rho m / t), rho = q mod t.
 __device__ __forceinline__ uint64_t round_rho(uint64_t m, const Consts& C) {

@@ -296,6 +296,17 @@ static pencil_status resolve_params(const pencil_params* p, pencil_ctx* ctx) {
     lc.r64_sh = shoup(lc.r64, ql);
     lc.r128 = (uint64_t)(((u128)lc.r64 * lc.r64) % ql);
     lc.r192 = (uint64_t)(((u128)lc.r128 * lc.r64) % ql);
+    {
+      const uint64_t r96 = (uint64_t)(((u128)lc.r64 << 32) % ql);
+      auto split = [](uint64_t v) { return (v & 0x3FFFFFFFull) | ((v >> 30) << 32); };
+      lc.r64_split = split(lc.r64);
+      lc.r96_split = split(r96);
+      const u128 ofs = ((u128)1 + ((u128)1 << 32) + lc.r64 + r96) % ql;
+      lc.mx_off = (uint64_t)((ql - (ofs << 56) % ql) % ql);
+      const uint64_t d60 = (1ull << 60) - ql;
+      lc.delta60 = d60 <= (1ull << 26) ? (uint32_t)d60 : 0;
+      C.fold60 = (l == 0 || C.fold60) && lc.delta60 != 0;
+    }
     lc.one_sh = (uint64_t)((((u128)1) << 64) / ql);
     lc.ninv = powmod(n, ql - 2, ql);
     lc.ninv_sh = shoup(lc.ninv, ql);
@@ -576,6 +587,7 @@ static bool make_geo(const OpGeom& g, const pencil_tile& t, int n, Geo* G) {
   o.dv_kw = recip(o.kw);
   o.dv_khw = recip((int64_t)o.kh * o.kw);
   o.dv_kthw = recip((int64_t)o.kt * o.kh * o.kw);
+  o.dv_sp = recip((int64_t)o.nOY * o.nOX);
   return true;
 }
 
@@ -867,7 +879,7 @@ extern "C" pencil_status pencil_encrypt(pencil_ctx* ctx, const pencil_layer* L, 
   const int64_t count = side ? n_k_tiles(G) : n_a_tiles(G);
   hipStream_t s = (hipStream_t)stream;
   uint64_t* u = (uint64_t*)ws;  // u^ of every ciphertext, [count][L][N]
-  hipError_t e = timed(ctx, KID_NTT_TERNARY, s, [&] { return launch_ntt_ternary(u, count, nonce, enc_object(operand, 0), P_ENC_U, 0, ctx->C, ctx->T, s); });
+  hipError_t e = timed(ctx, KID_NTT_TERNARY, s, [&] { return launch_ntt_ternary(u, count, nonce, enc_object(operand, 0), P_ENC_U, FORM_PLAIN, ctx->C, ctx->T, s); });
   if (e == hipSuccess)
     e = timed(ctx, KID_ENCRYPT, s, [&] {
       return launch_encrypt(u, share, ct, count, side, G, V, ctx->d_pk_ntt, ctx->d_pk_sh, nonce,
@@ -875,6 +887,30 @@ extern "C" pencil_status pencil_encrypt(pencil_ctx* ctx, const pencil_layer* L, 
     });
   if (e != hipSuccess) return fail(ctx, PENCIL_EHIP, "encrypt launch: %s", hipGetErrorString(e));
   return PENCIL_OK;
+}
+
+// Whether a product's multiply-accumulate runs on the matrix cores
+// (k_macx.hip).  First what that kernel's index arithmetic takes: contraction
+// sums within int32, reciprocal divisions of rows, evenly spaced tiles along the
+// contraction, tile numbers below 2^31.  Then the cheaper of two linear models
+// fitted to both kernels' times at N = 8192, L = 3 (13 output grids from 1 x 1 to
+// 33 x 3 tiles, 2 to 128 contraction indices, one and two terms; in ns for 1536
+// slot groups): a 16 x 16 output tile costs 30 us and 13 us per block of 16
+// indices however few of its rows are real, an output of the vector kernel (in
+// 2 x 2 blocks) 0.2 us and 0.0235 us per index.  Near the line both take about
+// the same (8 x 16 outputs, 16 indices: 52 against 62 us; 10 x 32, 13: 176
+// against 159), far from it the ratio reaches 2.2 (16 x 16, 128) and 0.1 (1 x 1).
+// Fewer workgroups than two per CU leave the matrix kernel, with one workgroup
+// per CU and a long prologue, half idle.
+static bool mac_use_matrix(const Consts& C, int n_terms, int m_rows, const Geo& G) {
+  const int64_t ksteps = (int64_t)G.nK * G.nKY * G.nKX, sp = (int64_t)G.nOY * G.nOX;
+  if (ksteps * n_terms > kMxMaxK || m_rows >= (1 << 15) || (sp > 1 && G.nKY * G.nKX > 1) || sp >= 256) return false;
+  if ((n_a_tiles(G) | n_k_tiles(G) | n_out_tiles(G)) >> 31) return false;
+  const int64_t tiles = mac_matrix_tiles(n_terms, m_rows, G.nR), total = mac_matrix_groups(C.n, C.L) * tiles;
+  if (total < 512 || total >= (1ll << 31)) return false;
+  const int64_t blocks = (ksteps + 15) / 16 * n_terms;
+  const int64_t outputs = ((int64_t)m_rows + 1) / 2 * 2 * (((int64_t)G.nR + 1) / 2 * 2);
+  return tiles * (30000 + 13000 * blocks) < outputs * (2000 + 235 * ksteps * n_terms) / 10;
 }
 
 // Element offset from a staged component-0 copy to component 1 of the same
@@ -903,6 +939,8 @@ static pencil_status run_product(pencil_ctx* ctx, const pencil_layer* L, int op,
   const int64_t poly = (int64_t)C.L * C.n, ctw = 2 * poly;
   const int64_t na = n_a_tiles(G), nk = n_k_tiles(G), no = n_out_tiles(G);
   uint64_t* w = (uint64_t*)ws;
+  const bool matrix = mac_use_matrix(C, n_terms, G.nM * G.nOY * G.nOX, G);
+  const int form_a = matrix ? FORM_DIGITS : FORM_SPLIT, form_k = matrix ? FORM_REVERSED : FORM_SPLIT;
   MacArgs A{};
   A.n_terms = n_terms;
   A.m_rows = G.nM * G.nOY * G.nOX;
@@ -921,28 +959,34 @@ static pencil_status run_product(pencil_ctx* ctx, const pencil_layer* L, int op,
       hipError_t e = hipSuccess;
       MacTerm mt{T.ct, pts, poly, 1, 0};
       if (add_share) {
-        e = timed(ctx, KID_NTT_CT, s, [&] { return launch_ntt_ct(T.ct, cts, na, add_share, G, view_a(L, op), C, ctx->T, s); });
-        mt.a = cts;
-        mt.c1 = comp1_offset(cts, T.ct, poly);
+        e = timed(ctx, KID_NTT_CT, s, [&] { return launch_ntt_ct(T.ct, cts, form_a, na, add_share, G, view_a(L, op), C, ctx->T, s); });
+        if (matrix) {
+          A.stage = cts;
+        } else {
+          mt.a = cts;
+          mt.c1 = comp1_offset(cts, T.ct, poly);
+        }
       }
       if (e == hipSuccess)
-        e = timed(ctx, KID_NTT_PT, s, [&] { return launch_ntt_pt(T.pt, pts, nk, 1, G, view_k(L, op), C, ctx->T, s); });
+        e = timed(ctx, KID_NTT_PT, s, [&] { return launch_ntt_pt(T.pt, pts, form_k, nk, 1, G, view_k(L, op), C, ctx->T, s); });
       if (e != hipSuccess) return fail(ctx, PENCIL_EHIP, "ntt launch: %s", hipGetErrorString(e));
       A.term[i] = mt;
     } else {
       uint64_t* pts = w;
       w += na * poly;
       w += nk * ctw;
-      hipError_t e = timed(ctx, KID_NTT_PT, s, [&] { return launch_ntt_pt(T.pt, pts, na, 0, G, view_a(L, op), C, ctx->T, s); });
+      hipError_t e = timed(ctx, KID_NTT_PT, s, [&] { return launch_ntt_pt(T.pt, pts, form_a, na, 0, G, view_a(L, op), C, ctx->T, s); });
       if (e != hipSuccess) return fail(ctx, PENCIL_EHIP, "ntt launch: %s", hipGetErrorString(e));
       A.term[i] = MacTerm{pts, T.ct, poly, 0, 0};
     }
   }
   uint64_t* u = w;
   const uint64_t obj = out_object(op, 0);
-  hipError_t e = timed(ctx, KID_NTT_TERNARY, s, [&] { return launch_ntt_ternary(u, no, nonce, obj, P_RR_U, 1, C, ctx->T, s); });
+  hipError_t e = timed(ctx, KID_NTT_TERNARY, s, [&] { return launch_ntt_ternary(u, no, nonce, obj, P_RR_U, matrix ? FORM_BLOCKED_SPLIT : FORM_SPLIT, C, ctx->T, s); });
   A.u = u;
-  if (e == hipSuccess) e = timed(ctx, KID_MAC, s, [&] { return launch_mac(A, no, G, C, s); });
+  if (e == hipSuccess) e = timed(ctx, KID_MAC, s, [&] {
+      return matrix ? launch_mac_matrix(A, G, C, s) : launch_mac(A, no, G, C, s);
+    });
   if (e == hipSuccess) e = timed(ctx, KID_INTT_OUT, s, [&] { return launch_ntt_plain(ct_out, 2 * no, true, C, ctx->T, s); });
   if (e == hipSuccess)
     e = timed(ctx, KID_FLOOD, s, [&] {
@@ -1321,6 +1365,9 @@ extern "C" pencil_status pencil_stride_relayout(pencil_ctx* ctx, const pencil_la
 
 // ------------------------------------------------------------ batched step
 
+// Key of the matrix-core multiply-accumulate's phase (after the schedule kinds).
+constexpr int kMacMatrix = kMacVariants / 3;
+
 struct pencil_step {
   struct Entry {
     int ctx;
@@ -1506,7 +1553,7 @@ static pencil_status step_bind_tables(pencil_step* st, const pencil_step_io* io,
     for (auto& e : st->layers) {
       const Consts& C = st->ctxs[e.ctx]->C;
       if (kind == 1) {  // each multiply-accumulate kernel kind launches separately
-        for (int k = 0; k < kMacVariants / 3; ++k) phase_for(st, 1, k);
+        for (int k = 0; k < kMacVariants / 3 + 1; ++k) phase_for(st, 1, k);
       } else {
         phase_for(st, kind, kind == 3 ? C.flood_words : C.log2n * 8 + C.ntt_loge);
       }
@@ -1540,6 +1587,8 @@ static pencil_status step_bind_tables(pencil_step* st, const pencil_step_io* io,
       if (A.variant < 0 || A.variant >= kMacVariants) return step_fail(st, PENCIL_EINVAL, "schedule variant invalid");
       A.pk = ctx->d_pk_split;
       A.out = ct_out;
+      const bool matrix = mac_use_matrix(C, op == 2 ? 2 : 1, A.m_rows, G);
+      const int form_a = matrix ? FORM_DIGITS : FORM_SPLIT, form_k = matrix ? FORM_REVERSED : FORM_SPLIT;
       StepSeg base{};
       base.ctx = e.ctx;
       base.G = G;
@@ -1559,9 +1608,15 @@ static pencil_status step_bind_tables(pencil_step* st, const pencil_step_io* io,
           sc.dst = cts;
           sc.tensor = add_share;
           sc.V = view_a(L, op);
+          sc.form = form_a;
+          sc.count = na;
           add_seg(ntt, sc, na * C.L);
-          mt.a = cts;
-          mt.c1 = comp1_offset(cts, ct_a, poly);
+          if (matrix) {
+            A.stage = cts;
+          } else {
+            mt.a = cts;
+            mt.c1 = comp1_offset(cts, ct_a, poly);
+          }
         }
         StepSeg sp = base;
         sp.kind = SEG_PT;
@@ -1569,6 +1624,8 @@ static pencil_status step_bind_tables(pencil_step* st, const pencil_step_io* io,
         sp.tensor = pt_k;
         sp.dst = pts;
         sp.V = view_k(L, op);
+        sp.form = form_k;
+        sp.count = nk;
         add_seg(ntt, sp, nk * C.L);
         A.term[0] = mt;
         A.n_terms = 1;
@@ -1583,6 +1640,8 @@ static pencil_status step_bind_tables(pencil_step* st, const pencil_step_io* io,
         sp.tensor = b.x0;
         sp.dst = pts;
         sp.V = view_a(L, op);
+        sp.form = form_a;
+        sp.count = na;
         add_seg(ntt, sp, na * C.L);
         A.term[1] = MacTerm{pts, b.ct_dy_dw, poly, 0, 0};
         A.n_terms = 2;
@@ -1594,14 +1653,18 @@ static pencil_status step_bind_tables(pencil_step* st, const pencil_step_io* io,
       su.nonce_off = nonce_off;
       su.obj_base = out_object(op, 0);
       su.purpose = P_RR_U;
+      su.form = matrix ? FORM_BLOCKED_SPLIT : FORM_SPLIT;
+      su.count = no;
       add_seg(ntt, su, no * C.L);
       A.u = u;
       StepSeg sm = base;
       sm.kind = SEG_MAC;
       sm.mac = A;
-      sm.slot_blocks = (int64_t)C.n * C.L / 64;
-      const int64_t chunks = mac_chunks(A.variant, A.m_rows, G.nR);
-      add_seg(phase_for(st, 1, A.variant / 3), sm, (sm.slot_blocks * chunks + 7) & ~(int64_t)7);
+      sm.slot_blocks = matrix ? mac_matrix_groups(C.n, C.L) : (int64_t)C.n * C.L / 64;
+      const int64_t chunks =
+          matrix ? mac_matrix_tiles(A.n_terms, A.m_rows, G.nR) : mac_chunks(A.variant, A.m_rows, G.nR);
+      add_seg(phase_for(st, 1, matrix ? kMacMatrix : A.variant / 3), sm,
+              (sm.slot_blocks * chunks + 7) & ~(int64_t)7);
       StepSeg si = base;
       si.kind = SEG_INTT;
       si.dst = ct_out;
@@ -1644,7 +1707,9 @@ static hipError_t step_phases(pencil_step* st, hipStream_t s) {
       e = timed(pc, ph.kind == 0 ? KID_STEP_NTT : KID_STEP_INTT, s,
                 [&] { return launch_step_ntt(ph.key / 8, ph.key % 8, ph.kind == 2, P, ph.blocks, s); });
     else if (ph.kind == 1)
-      e = timed(pc, KID_STEP_MAC, s, [&] { return launch_step_mac(P, ph.blocks, ph.key, s); });
+      e = timed(pc, KID_STEP_MAC, s, [&] { 
+        return ph.key == kMacMatrix ? launch_step_mac_matrix(P, ph.blocks, s) : launch_step_mac(P, ph.blocks, ph.key, s);
+      });
     else
       e = timed(pc, KID_STEP_FLOOD, s, [&] { return launch_step_flood(ph.key, P, ph.blocks, s); });
     if (e != hipSuccess) return e;

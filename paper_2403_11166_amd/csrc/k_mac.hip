@@ -439,13 +439,6 @@ __device__ __forceinline__ void fold_lds(Part<SPLIT> (&acc)[8], u64x2* tot, uint
   }
 }
 
-// A wave-uniform 64-bit pointer, kept in scalar registers.
-__device__ __forceinline__ const char* uni(const char* p) {
-  const uint64_t v = (uint64_t)p;
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return (const char*)(((uint64_t)hi << 32) | lo);
-}
-
 // Load at uniform base + per-lane byte offset (a scalar base and a 32-bit vector offset).
 __device__ __forceinline__ uint64_t ld(const char* base, uint32_t off) {
   return *(const PENCIL_GLOBAL uint64_t*)((const PENCIL_GLOBAL char*)base + off);

@@ -1127,7 +1127,8 @@ hipError_t scratch_address(int device, void** out) {
 }
 
 hipError_t configure_lds_limits() {
-  hipError_t e[4] = {configure_lds_ntt(), configure_lds_mac(), configure_lds_do(), configure_lds_step()};
+  hipError_t e[5] = {configure_lds_ntt(), configure_lds_mac(), configure_lds_macx(), configure_lds_do(),
+                     configure_lds_step()};
   for (hipError_t x : e)
     if (x != hipSuccess) return x;
   return hipSuccess;

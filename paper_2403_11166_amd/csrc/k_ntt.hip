@@ -11,24 +11,24 @@ __global__ void PENCIL_NTT_BOUNDS(LOGN, LOGE) k_ntt_plain(uint64_t* data, int in
 }
 
 template <int LOGN, int LOGE>
-__global__ void PENCIL_NTT_BOUNDS(LOGN, LOGE) k_ntt_ct(const uint64_t* src, uint64_t* dst, const int64_t* share, Geo G,
-                                                 View V, Consts C, Tables T) {
+__global__ void PENCIL_NTT_BOUNDS(LOGN, LOGE) k_ntt_ct(const uint64_t* src, uint64_t* dst, int form, int64_t count,
+                                                       const int64_t* share, Geo G, View V, Consts C, Tables T) {
   extern __shared__ uint64_t lds[];
-  do_ntt_ct<LOGN, LOGE>(lds, src, dst, share, G, V, C, T, blockIdx.x);
+  do_ntt_ct<LOGN, LOGE>(lds, src, dst, form, count, share, G, V, C, T, blockIdx.x);
 }
 
 template <int LOGN, int LOGE>
-__global__ void PENCIL_NTT_BOUNDS(LOGN, LOGE) k_ntt_pt(const int64_t* tensor, uint64_t* dst, int side, Geo G, View V,
-                                                 Consts C, Tables T) {
+__global__ void PENCIL_NTT_BOUNDS(LOGN, LOGE) k_ntt_pt(const int64_t* tensor, uint64_t* dst, int form, int64_t count,
+                                                       int side, Geo G, View V, Consts C, Tables T) {
   extern __shared__ uint64_t lds[];
-  do_ntt_pt<LOGN, LOGE>(lds, tensor, dst, side, G, V, C, T, blockIdx.x);
+  do_ntt_pt<LOGN, LOGE>(lds, tensor, dst, form, count, side, G, V, C, T, blockIdx.x);
 }
 
 template <int LOGN, int LOGE>
 __global__ void PENCIL_NTT_BOUNDS(LOGN, LOGE) k_ntt_ternary(uint64_t* dst, uint64_t nonce, uint64_t obj_base,
-                                                      uint32_t purpose, int split, Consts C, Tables T) {
+                                                      uint32_t purpose, int form, int64_t count, Consts C, Tables T) {
   extern __shared__ uint64_t lds[];
-  do_ntt_ternary<LOGN, LOGE>(lds, dst, nonce, obj_base, purpose, split, C, T, blockIdx.x);
+  do_ntt_ternary<LOGN, LOGE>(lds, dst, nonce, obj_base, purpose, form, count, C, T, blockIdx.x);
 }
 
 hipError_t launch_ntt_plain(uint64_t* data, int64_t polys, bool inverse, const Consts& C, const Tables& T,
@@ -38,24 +38,24 @@ hipError_t launch_ntt_plain(uint64_t* data, int64_t polys, bool inverse, const C
   return hipGetLastError();
 }
 
-hipError_t launch_ntt_ct(const uint64_t* src, uint64_t* dst, int64_t n_ct, const int64_t* share, const Geo& G,
+hipError_t launch_ntt_ct(const uint64_t* src, uint64_t* dst, int form, int64_t n_ct, const int64_t* share, const Geo& G,
                          const View& V, const Consts& C, const Tables& T, hipStream_t s) {
   if (n_ct <= 0) return hipSuccess;
-  NTT_DISPATCH(k_ntt_ct, dim3((unsigned)(n_ct * C.L)), C, s, src, dst, share, G, V, C, T);
+  NTT_DISPATCH(k_ntt_ct, dim3((unsigned)(n_ct * C.L)), C, s, src, dst, form, n_ct, share, G, V, C, T);
   return hipGetLastError();
 }
 
-hipError_t launch_ntt_pt(const int64_t* tensor, uint64_t* dst, int64_t n_pt, int side, const Geo& G, const View& V,
+hipError_t launch_ntt_pt(const int64_t* tensor, uint64_t* dst, int form, int64_t n_pt, int side, const Geo& G, const View& V,
                          const Consts& C, const Tables& T, hipStream_t s) {
   if (n_pt <= 0) return hipSuccess;
-  NTT_DISPATCH(k_ntt_pt, dim3((unsigned)(n_pt * C.L)), C, s, tensor, dst, side, G, V, C, T);
+  NTT_DISPATCH(k_ntt_pt, dim3((unsigned)(n_pt * C.L)), C, s, tensor, dst, form, n_pt, side, G, V, C, T);
   return hipGetLastError();
 }
 
-hipError_t launch_ntt_ternary(uint64_t* dst, int64_t count, uint64_t nonce, uint64_t obj_base, uint32_t purpose, int split,
+hipError_t launch_ntt_ternary(uint64_t* dst, int64_t count, uint64_t nonce, uint64_t obj_base, uint32_t purpose, int form,
                               const Consts& C, const Tables& T, hipStream_t s) {
   if (count <= 0) return hipSuccess;
-  NTT_DISPATCH(k_ntt_ternary, dim3((unsigned)(count * C.L)), C, s, dst, nonce, obj_base, purpose, split, C, T);
+  NTT_DISPATCH(k_ntt_ternary, dim3((unsigned)(count * C.L)), C, s, dst, nonce, obj_base, purpose, form, count, C, T);
   return hipGetLastError();
 }
 

@@ -17,9 +17,9 @@ __global__ void PENCIL_NTT_BOUNDS(LOGN, LOGE)
   const Tables& T = tabs[S.ctx];
   const int64_t p = (int64_t)blockIdx.x - S.block_begin;
   switch (S.kind) {
-    case SEG_CT: do_ntt_ct<LOGN, LOGE>(lds, S.src, S.dst, S.tensor, S.G, S.V, C, T, p); break;
-    case SEG_PT: do_ntt_pt<LOGN, LOGE>(lds, S.tensor, S.dst, S.side, S.G, S.V, C, T, p); break;
-    case SEG_TERN: do_ntt_ternary<LOGN, LOGE>(lds, S.dst, *nonce + S.nonce_off, S.obj_base, S.purpose, 1, C, T, p); break;
+    case SEG_CT: do_ntt_ct<LOGN, LOGE>(lds, S.src, S.dst, S.form, S.count, S.tensor, S.G, S.V, C, T, p); break;
+    case SEG_PT: do_ntt_pt<LOGN, LOGE>(lds, S.tensor, S.dst, S.form, S.count, S.side, S.G, S.V, C, T, p); break;
+    case SEG_TERN: do_ntt_ternary<LOGN, LOGE>(lds, S.dst, *nonce + S.nonce_off, S.obj_base, S.purpose, S.form, S.count, C, T, p); break;
     default: break;
   }
 }

@@ -302,11 +302,13 @@ __device__ __forceinline__ void do_ntt_plain(uint64_t* lds, uint64_t* data, int 
 // model owner's share: component 0 gains the transform of round(q m / t) of
 // the share (Alg. 1, product step) and is written, split, to the staging
 // copy; component 1 is read in place by the multiply-accumulate.
-// Grid: n_ct * L blocks, polynomial p = (j, l) in [n][L] order; src and dst
-// are [n][2][L][N].
+// Grid: count * L blocks, polynomial p = (j, l) in [count][L] order; src is
+// [count][2][L][N], and so is dst (component 0 only) in split form; for the
+// matrix-core multiply-accumulate dst holds component 0 alone, in `form`.
 template <int LOGN, int LOGE>
-__device__ __forceinline__ void do_ntt_ct(uint64_t* lds, const uint64_t* src, uint64_t* dst, const int64_t* share,
-                                          const Geo& G, const View& V, const Consts& C, const Tables& T, int64_t p) {
+__device__ __forceinline__ void do_ntt_ct(uint64_t* lds, const uint64_t* src, uint64_t* dst, int form, int64_t count,
+                                          const int64_t* share, const Geo& G, const View& V, const Consts& C,
+                                          const Tables& T, int64_t p) {
   constexpr int n = 1 << LOGN;
   const int L = C.L;
   const int l = (int)(p % L);
@@ -327,6 +329,18 @@ __device__ __forceinline__ void do_ntt_ct(uint64_t* lds, const uint64_t* src, ui
   ntt_fwd_in<LOGN, LOGE>(lds, enc, T.fw + (int64_t)l * n, lc.q);
   // 16-byte accesses: a polynomial is 16-byte aligned
   const PENCIL_GLOBAL u64x2* g2 = (const PENCIL_GLOBAL u64x2*)gview(src + at);
+  if (form_blocked(form)) {
+    PENCIL_GLOBAL uint64_t* o = gview(dst + ((int64_t)l * (n / kMxGroup) * count + j) * kMxGroup);
+    const int64_t group = count * kMxGroup;
+    for (int i = threadIdx.x; i < n / 2; i += blockDim.x) {
+      const u64x2 v = g2[i];
+      const int s = 2 * i;
+      *(PENCIL_GLOBAL u64x2*)(o + (s / kMxGroup) * group + s % kMxGroup) =
+          u64x2{form_value(add_mod(unsplit30(v[0]), lds[lpad(s)], lc.q), form),
+                form_value(add_mod(unsplit30(v[1]), lds[lpad(s) + 1], lc.q), form)};
+    }
+    return;
+  }
   PENCIL_GLOBAL u64x2* o2 = (PENCIL_GLOBAL u64x2*)gview(dst + at);
   for (int i = threadIdx.x; i < n / 2; i += blockDim.x) {
     const u64x2 v = g2[i];
@@ -336,10 +350,11 @@ __device__ __forceinline__ void do_ntt_ct(uint64_t* lds, const uint64_t* src, ui
 }
 
 // Plaintext tiles: encode (side 0: forward A tile, 1: reverse K tile), centred
-// lift of Z_t into Z_{q_l}, forward NTT.  Grid: n_pt * L, output [n][L][N].
+// lift of Z_t into Z_{q_l}, forward NTT.  Grid: count * L, output [count][L][N]
+// or slot-blocked, in `form`.
 template <int LOGN, int LOGE>
-__device__ __forceinline__ void do_ntt_pt(uint64_t* lds, const int64_t* tensor, uint64_t* dst, int side,
-                                          const Geo& G, const View& V, const Consts& C, const Tables& T, int64_t p) {
+__device__ __forceinline__ void do_ntt_pt(uint64_t* lds, const int64_t* tensor, uint64_t* dst, int form, int64_t count,
+                                          int side, const Geo& G, const View& V, const Consts& C, const Tables& T, int64_t p) {
   constexpr int n = 1 << LOGN;
   const int L = C.L;
   const int l = (int)(p % L);
@@ -372,20 +387,17 @@ __device__ __forceinline__ void do_ntt_pt(uint64_t* lds, const int64_t* tensor, 
     __syncthreads();
     ntt_fwd<LOGN, LOGE>(lds, T.fw + (int64_t)l * n, lc.q);
   }
-  PENCIL_GLOBAL uint64_t* o = gview(dst + p * n);
-  PENCIL_GLOBAL u64x2* o2 = (PENCIL_GLOBAL u64x2*)o;
-  for (int i = threadIdx.x; i < n / 2; i += blockDim.x)
-    o2[i] = u64x2{split30(lds[lpad(2 * i)]), split30(lds[lpad(2 * i) + 1])};
+  store_form<LOGN>(dst, form, count, L, l, j, [&](int i) { return form_value(lds[lpad(i)], form); });
 }
 
 // Fresh ternary polynomials (object obj_base + j, stream `purpose`), lifted and
 // transformed.  Coefficient i uses the 32-bit half i mod 2 of stream word i/2,
-// so one Philox block covers 8 coefficients.  Grid: count * L, output [n][L][N],
-// in the multiply-accumulate's split form when `split` is set.
+// so one Philox block covers 8 coefficients.  Grid: count * L, output
+// [count][L][N] or slot-blocked, in `form`.
 template <int LOGN, int LOGE>
 __device__ __forceinline__ void do_ntt_ternary(uint64_t* lds, uint64_t* dst, uint64_t nonce, uint64_t obj_base,
-                                               uint32_t purpose, int split, const Consts& C, const Tables& T,
-                                               int64_t p) {
+                                               uint32_t purpose, int form, int64_t count, const Consts& C,
+                                               const Tables& T, int64_t p) {
   constexpr int n = 1 << LOGN;
   const int L = C.L;
   const int l = (int)(p % L);
@@ -401,12 +413,7 @@ __device__ __forceinline__ void do_ntt_ternary(uint64_t* lds, uint64_t* dst, uin
   }
   __syncthreads();
   ntt_fwd<LOGN, LOGE>(lds, T.fw + (int64_t)l * n, lc.q);
-  PENCIL_GLOBAL u64x2* o2 = (PENCIL_GLOBAL u64x2*)gview(dst + p * n);
-  if (split)
-    for (int i = threadIdx.x; i < n / 2; i += blockDim.x)
-      o2[i] = u64x2{split30(lds[lpad(2 * i)]), split30(lds[lpad(2 * i) + 1])};
-  else
-    for (int i = threadIdx.x; i < n / 2; i += blockDim.x) o2[i] = u64x2{lds[lpad(2 * i)], lds[lpad(2 * i) + 1]};
+  store_form<LOGN>(dst, form, count, L, l, j, [&](int i) { return form_value(lds[lpad(i)], form); });
 }
 
 }  // namespace pencil

@@ -13,6 +13,10 @@ struct LimbConst {
   uint64_t q;
   uint64_t r64, r64_sh;          // 2^64 mod q
   uint64_t r128, r192;           // 2^128 mod q, 2^192 mod q
+  // matrix-core multiply-accumulate: 2^64 and 2^96 mod q in split form,
+  // -2^56 (1 + 2^32 + 2^64 + 2^96) mod q, and 2^60 - q where that is at most 2^26 (else 0)
+  uint64_t r64_split, r96_split, mx_off;
+  uint32_t delta60, pad0;
   uint64_t one_sh;               // floor(2^64 / q)
   uint64_t ninv, ninv_sh;        // N^-1 mod q
   uint64_t delta, delta_sh;      // floor(q / t) mod q_l
@@ -28,6 +32,7 @@ struct Consts {
   uint32_t flood_bits, mac_chunk, qwords;
   int32_t ntt_loge;              // log2 of the residues each NTT thread keeps (4 or 5)
   uint32_t mac_fold, mac_fold4;  // MAC steps per fold of the 64-bit partial sums (three, four sums)
+  uint32_t fold60, pad0;         // every limb has delta60
   uint64_t t, t_half;            // t and (t - 1) / 2
   uint64_t rho, rho_sh;          // q mod t, floor(rho * 2^64 / t)
   uint64_t r64t, r64t_sh;        // 2^64 mod t and floor(r64t * 2^64 / t)
@@ -63,7 +68,7 @@ struct Geo {
   // and of kw, kh*kw, kt*kh*kw for enumerating a K tile's entries (0 for
   // d = 1): floor(n / d) = umulhi(n, m) for n, d < 2^16.
   uint32_t dv_rs, dv_hw, dv_wa, dv_s;
-  uint32_t dv_kw, dv_khw, dv_kthw, pad2;
+  uint32_t dv_kw, dv_khw, dv_kthw, dv_sp;  // sp = nOY nOX
 };
 
 // Maps virtual coordinates (i0, i1, y, x) of an operand to an element offset of
@@ -87,6 +92,11 @@ constexpr uint64_t kKeygenNonce = ~0ull;
 inline uint64_t enc_object(int operand, uint64_t i) { return ((uint64_t)(operand + 1) << 48) | i; }
 inline uint64_t out_object(int op, uint64_t i) { return ((uint64_t)(op + 5) << 48) | i; }
 
+// Slots per group of the slot-blocked buffers (a 512-byte run), and the forms
+// the forward transforms write (form_value, store_form).
+constexpr int kMxGroup = 64;
+enum Form : int32_t { FORM_PLAIN = 0, FORM_SPLIT = 1, FORM_DIGITS = 2, FORM_REVERSED = 3, FORM_BLOCKED_SPLIT = 4 };
+
 // One term of a product: which side holds the ciphertext and where both operands live
 // (NTT domain, split form).  ct: [n][2][L][N] (component 0 addresses); pt: [n][L][N].
 // A ciphertext's component 1 sits c1 elements after its component 0: L*N in the
@@ -107,7 +117,8 @@ struct MacArgs {
   int32_t variant;     // multiply-accumulate schedule (0..kMacVariants-1), see mac_rows
   int32_t pad;
   const uint64_t* pk;  // [2][L][N], NTT domain, split form
-  const uint64_t* u;   // [n_out][L][N], NTT domain
+  const uint64_t* u;   // [n_out][L][N], NTT domain (slot-blocked for the matrix cores)
+  const uint64_t* stage;  // matrix cores: component 0 of term 0 with the share added, or null
   uint64_t* out;       // [n_out][2][L][N]
 };
 
@@ -118,8 +129,8 @@ enum SegKind : int32_t { SEG_CT = 0, SEG_PT = 1, SEG_TERN = 2, SEG_INTT = 3, SEG
 
 struct StepSeg {
   int64_t block_begin;       // first block of the segment in its phase grid
-  int32_t kind, ctx, side, purpose;
-  int64_t count;             // flood: number of output ciphertexts
+  int32_t kind, ctx, side, purpose, form, pad;
+  int64_t count;             // flood: output ciphertexts; forward NTTs: tiles of the operand
   int64_t slot_blocks;       // mac: 64-slot groups (work items = slot_blocks x chunks)
   uint64_t nonce_off, obj_base;
   const uint64_t* src;
@@ -157,17 +168,28 @@ __host__ __device__ inline int mac_chunks(int variant, int m_rows, int n_r) {
   return ((m_rows + mac_rows(variant) - 1) / mac_rows(variant)) * ((n_r + mac_cols(variant) - 1) / mac_cols(variant));
 }
 
+// Matrix-core multiply-accumulate: work per group of 16 NTT slots, in 16 x 16
+// output tiles whose rows are (A row, component) pairs for one term, A rows of
+// one component for two.
+constexpr int kMxMaxK = 8192;  // contraction indices (all terms) its int32 accumulators hold
+__host__ __device__ inline int mac_matrix_tiles(int n_terms, int m_rows, int n_r) {
+  const int rt = n_terms == 1 ? (2 * m_rows + 15) / 16 : 2 * ((m_rows + 15) / 16);
+  return rt * ((n_r + 15) / 16);
+}
+__host__ __device__ inline int64_t mac_matrix_groups(int n, int limbs) { return (int64_t)n * limbs / 16; }
+
 // ---------------------------------------------------------------- launchers
 // (defined in kernels.hip; all enqueue on `stream` and return the launch status)
 hipError_t launch_ntt_plain(uint64_t* data, int64_t polys, bool inverse, const Consts& C, const Tables& T,
                             hipStream_t s);
-hipError_t launch_ntt_ct(const uint64_t* src, uint64_t* dst, int64_t n_ct, const int64_t* share, const Geo& G,
+hipError_t launch_ntt_ct(const uint64_t* src, uint64_t* dst, int form, int64_t n_ct, const int64_t* share, const Geo& G,
                          const View& V, const Consts& C, const Tables& T, hipStream_t s);
-hipError_t launch_ntt_pt(const int64_t* tensor, uint64_t* dst, int64_t n_pt, int side, const Geo& G, const View& V,
+hipError_t launch_ntt_pt(const int64_t* tensor, uint64_t* dst, int form, int64_t n_pt, int side, const Geo& G, const View& V,
                          const Consts& C, const Tables& T, hipStream_t s);
-hipError_t launch_ntt_ternary(uint64_t* dst, int64_t count, uint64_t nonce, uint64_t obj_base, uint32_t purpose, int split,
+hipError_t launch_ntt_ternary(uint64_t* dst, int64_t count, uint64_t nonce, uint64_t obj_base, uint32_t purpose, int form,
                               const Consts& C, const Tables& T, hipStream_t s);
 hipError_t launch_mac(const MacArgs& A, int64_t n_out, const Geo& G, const Consts& C, hipStream_t s);
+hipError_t launch_mac_matrix(const MacArgs& A, const Geo& G, const Consts& C, hipStream_t s);
 hipError_t launch_flood_mask(uint64_t* ct, int64_t n_out, int64_t* share0, const int64_t* bias, const Geo& G,
                              const View& outV, uint64_t nonce, uint64_t obj_base, const Consts& C, hipStream_t s);
 hipError_t launch_encrypt(const uint64_t* u_ntt, const int64_t* share, uint64_t* ct, int64_t n_ct, int side,
@@ -205,6 +227,7 @@ hipError_t launch_zt_corr(const int64_t* a, const int64_t* k, int64_t* out, cons
                           const View& KV, const View& OV, const Consts& C, hipStream_t s);
 hipError_t launch_step_ntt(int log2n, int loge, bool inverse, const StepPhase& P, int64_t blocks, hipStream_t s);
 hipError_t launch_step_mac(const StepPhase& P, int64_t blocks, int kind, hipStream_t s);
+hipError_t launch_step_mac_matrix(const StepPhase& P, int64_t blocks, hipStream_t s);
 hipError_t launch_step_flood(int words, const StepPhase& P, int64_t blocks, hipStream_t s);
 hipError_t launch_set_u64(uint64_t* p, uint64_t v, int add, hipStream_t s);
 hipError_t launch_keygen(uint64_t* s_ntt, int64_t* s_coeff, uint64_t* pk_coeff, uint64_t* pk_ntt,
@@ -233,6 +256,7 @@ hipError_t scratch_address(int device, void** out);
 // function per translation unit, all called by configure_lds_limits().
 hipError_t configure_lds_ntt();
 hipError_t configure_lds_mac();
+hipError_t configure_lds_macx();
 hipError_t configure_lds_do();
 hipError_t configure_lds_step();
 hipError_t configure_lds_limits();
