@@ -219,23 +219,26 @@ __device__ __forceinline__ int find_seg(const StepSeg* segs, int nseg, int64_t b
 
 static inline size_t lds_bytes(const Consts& C) { return (size_t)(C.n + (C.n >> 5)) * sizeof(uint64_t); }
 
-// Instantiate `kern<LOGN>` for the context's degree and launch it.
-#define NTT_CASE(kern, LN, LE, grid, C, s, ...)                                                 \
-  case (LN) * 8 + (LE):                                                                          \
-    hipLaunchKernelGGL((kern<LN, LE>), grid, dim3((1u << (LN)) >> (LE)), lds_bytes(C), s, __VA_ARGS__); \
+// Instantiate `kern<LOGN, LOGE, F60>` for the context's degree, per-thread width
+// and kind of moduli, and launch it.
+#define NTT_CASE(kern, LN, LE, F, grid, C, s, ...)                                              \
+  case ((LN) * 8 + (LE)) * 2 + (F):                                                              \
+    hipLaunchKernelGGL((kern<LN, LE, F>), grid, dim3((1u << (LN)) >> (LE)), lds_bytes(C), s, __VA_ARGS__); \
     break;
-// Instantiate `kern<LOGN, LOGE>` for the context's degree and per-thread width.
+#define NTT_CASES(kern, LN, LE, grid, C, s, ...)      \
+  NTT_CASE(kern, LN, LE, false, grid, C, s, __VA_ARGS__) \
+  NTT_CASE(kern, LN, LE, true, grid, C, s, __VA_ARGS__)
 #define NTT_DISPATCH(kern, grid, C, s, ...)                                                \
   do {                                                                                     \
-    switch ((C).log2n * 8 + (C).ntt_loge) {                                                \
-      NTT_CASE(kern, 10, 4, grid, C, s, __VA_ARGS__)                                       \
-      NTT_CASE(kern, 11, 4, grid, C, s, __VA_ARGS__)                                       \
-      NTT_CASE(kern, 12, 4, grid, C, s, __VA_ARGS__)                                       \
-      NTT_CASE(kern, 12, 5, grid, C, s, __VA_ARGS__)                                       \
-      NTT_CASE(kern, 13, 4, grid, C, s, __VA_ARGS__)                                       \
-      NTT_CASE(kern, 13, 5, grid, C, s, __VA_ARGS__)                                       \
-      NTT_CASE(kern, 14, 4, grid, C, s, __VA_ARGS__)                                       \
-      NTT_CASE(kern, 14, 5, grid, C, s, __VA_ARGS__)                                       \
+    switch (((C).log2n * 8 + (C).ntt_loge) * 2 + ((C).fold60 ? 1 : 0)) {                   \
+      NTT_CASES(kern, 10, 4, grid, C, s, __VA_ARGS__)                                      \
+      NTT_CASES(kern, 11, 4, grid, C, s, __VA_ARGS__)                                      \
+      NTT_CASES(kern, 12, 4, grid, C, s, __VA_ARGS__)                                      \
+      NTT_CASES(kern, 12, 5, grid, C, s, __VA_ARGS__)                                      \
+      NTT_CASES(kern, 13, 4, grid, C, s, __VA_ARGS__)                                      \
+      NTT_CASES(kern, 13, 5, grid, C, s, __VA_ARGS__)                                      \
+      NTT_CASES(kern, 14, 4, grid, C, s, __VA_ARGS__)                                      \
+      NTT_CASES(kern, 14, 5, grid, C, s, __VA_ARGS__)                                      \
       default: return hipErrorInvalidValue;                                                \
     }                                                                                      \
   } while (0)

@@ -25,7 +25,7 @@ struct pencil_ctx {
   Tables T{};
   int device = 0;
   // device memory owned by the context
-  TW* d_tables = nullptr;        // forward then inverse twiddles, each [L][N]
+  TW* d_tables = nullptr;        // per NTT width (4, 5): forward then inverse twiddles, each [L][N]
   uint64_t* d_s_ntt = nullptr;   // [L][N]
   uint64_t* d_s_sh = nullptr;    // [L][N]
   uint64_t* d_pk_ntt = nullptr;  // [2][L][N]
@@ -264,7 +264,7 @@ static pencil_status resolve_params(const pencil_params* p, pencil_ctx* ctx) {
   C.log2n = (int32_t)p->log2_n;
   C.n = (int32_t)n;
   C.L = (int32_t)p->num_limbs;
-  C.ntt_loge = p->log2_n >= 14 ? 5 : 4;
+  C.ntt_loge = 4;
   C.flood_bits = fb;
   C.flood_words = (int32_t)((fb + 1 + 63) / 64);
   const int topbits = (int)(fb + 1) - 64 * (C.flood_words - 1);
@@ -308,8 +308,6 @@ static pencil_status resolve_params(const pencil_params* p, pencil_ctx* ctx) {
       C.fold60 = (l == 0 || C.fold60) && lc.delta60 != 0;
     }
     lc.one_sh = (uint64_t)((((u128)1) << 64) / ql);
-    lc.ninv = powmod(n, ql - 2, ql);
-    lc.ninv_sh = shoup(lc.ninv, ql);
     lc.delta = big_mod_small(delta, ql);
     lc.delta_sh = shoup(lc.delta, ql);
     lc.t_sh = shoup(t, ql);
@@ -366,6 +364,38 @@ static uint32_t bitrev(uint32_t x, int bits) {
   return r;
 }
 
+static uint64_t split30(uint64_t v) { return (v & 0x3FFFFFFFull) | ((v >> 30) << 32); }
+
+static TW twiddle(uint64_t w, uint64_t q, bool fold60) {
+  if (fold60) return TW{split30(w), split30((uint64_t)(((u128)w << 32) % q))};
+  return TW{w, shoup(w, q)};
+}
+
+// The natural table (entry k = psi^rev(k)) in the order in which a transform of
+// 2^loge residues per thread reads it: each pass, over 2^b blocks, keeps the
+// entries [2^b, 2^(b + size)), entry 2^(b + s) + (blk << s) + j of a block going to
+// ((2^s + j) << b) + blk.  Forward passes start at b = 0, inverse ones end there.
+static void pass_order(const TW* in, TW* out, int logn, int loge, bool inverse) {
+  out[0] = in[0];
+  for (int p = 0; p < ntt_pass_count(logn, loge); ++p) {
+    const int start = ntt_pass_start(logn, loge, p), size = ntt_pass_size(logn, loge, p);
+    const int b = inverse ? logn - start - size : start;
+    for (int s = 0; s < size; ++s)
+      for (size_t j = 0; j < (size_t)1 << s; ++j)
+        for (size_t blk = 0; blk < (size_t)1 << b; ++blk)
+          out[((((size_t)1 << s) + j) << b) + blk] = in[((size_t)1 << (b + s)) + (blk << s) + j];
+  }
+}
+
+// The context's residues per thread (log2), with the tables in its passes' order.
+static void set_ntt_loge(pencil_ctx* ctx, int loge) {
+  Consts& C = ctx->C;
+  const size_t ln = (size_t)C.L * C.n;
+  C.ntt_loge = loge;
+  ctx->T.fw = ctx->d_tables + 2 * (size_t)(loge - 4) * ln;
+  ctx->T.iw = ctx->T.fw + ln;
+}
+
 extern "C" pencil_status pencil_ctx_create(const pencil_params* params, pencil_ctx** out) {
   if (!out) return fail(nullptr, PENCIL_EINVAL, "out is NULL");
   *out = nullptr;
@@ -377,15 +407,27 @@ extern "C" pencil_status pencil_ctx_create(const pencil_params* params, pencil_c
   }
   const Consts& C = ctx->C;
   const size_t n = (size_t)C.n, L = (size_t)C.L;
-  // NTT tables: [L][N] pairs (w, floor(w 2^64 / q)) of psi^rev(k), then of psi^-rev(k)
-  std::vector<TW> tab(2 * L * n);
+  // NTT tables: [L][N] twiddles psi^rev(k), then psi^-rev(k), in the passes' order
+  // for each width the context can be tuned to
+  const int widths = C.log2n >= 12 ? 2 : 1;
+  std::vector<TW> tab(2 * widths * L * n);
   for (size_t l = 0; l < L; ++l) {
     const uint64_t q = C.limb[l].q, psi = ctx->info.psi[l], ipsi = powmod(psi, q - 2, q);
+    std::vector<TW> fw(n), iw(n);
     for (size_t k = 0; k < n; ++k) {
       uint32_t e = bitrev((uint32_t)k, C.log2n);
-      uint64_t w = powmod(psi, e, q), iw = powmod(ipsi, e, q);
-      tab[l * n + k] = TW{w, shoup(w, q)};
-      tab[L * n + l * n + k] = TW{iw, shoup(iw, q)};
+      uint64_t w = powmod(psi, e, q), iww = powmod(ipsi, e, q);
+      fw[k] = twiddle(w, q, C.fold60);
+      iw[k] = twiddle(iww, q, C.fold60);
+    }
+    // the last inverse stage multiplies by N^-1 as well
+    const uint64_t ninv = powmod(n, q - 2, q);
+    iw[0] = twiddle(ninv, q, C.fold60);
+    iw[1] = twiddle(mulmod(powmod(ipsi, bitrev(1, C.log2n), q), ninv, q), q, C.fold60);
+    for (int v = 0; v < widths; ++v) {
+      TW* out = tab.data() + 2 * v * L * n + l * n;
+      pass_order(fw.data(), out, C.log2n, 4 + v, false);
+      pass_order(iw.data(), out + L * n, C.log2n, 4 + v, true);
     }
   }
   auto cleanup = [&](pencil_status s) {
@@ -397,17 +439,16 @@ extern "C" pencil_status pencil_ctx_create(const pencil_params* params, pencil_c
   if (scratch_address(ctx->device, &ctx->d_scratch) != hipSuccess)
     return cleanup(fail(nullptr, PENCIL_EHIP, "no device address for the scratch array"));
   const size_t ln = L * n * sizeof(uint64_t);
-  if (hipMalloc(&ctx->d_tables, 2 * L * n * sizeof(TW)) != hipSuccess || hipMalloc(&ctx->d_s_ntt, ln) != hipSuccess ||
+  if (hipMalloc(&ctx->d_tables, tab.size() * sizeof(TW)) != hipSuccess || hipMalloc(&ctx->d_s_ntt, ln) != hipSuccess ||
       hipMalloc(&ctx->d_s_sh, ln) != hipSuccess || hipMalloc(&ctx->d_pk_ntt, 2 * ln) != hipSuccess ||
       hipMalloc(&ctx->d_pk_sh, 2 * ln) != hipSuccess || hipMalloc(&ctx->d_pk_coeff, 2 * ln) != hipSuccess ||
       hipMalloc(&ctx->d_pk_split, 2 * ln) != hipSuccess ||
       hipMalloc(&ctx->d_s_coeff, n * sizeof(int64_t)) != hipSuccess ||
       hipMalloc(&ctx->d_noise, 256) != hipSuccess)
     return cleanup(fail(nullptr, PENCIL_ENOMEM, "device allocation failed"));
-  if (hipMemcpy(ctx->d_tables, tab.data(), 2 * L * n * sizeof(TW), hipMemcpyHostToDevice) != hipSuccess)
+  if (hipMemcpy(ctx->d_tables, tab.data(), tab.size() * sizeof(TW), hipMemcpyHostToDevice) != hipSuccess)
     return cleanup(fail(nullptr, PENCIL_EHIP, "table upload failed"));
-  ctx->T.fw = ctx->d_tables;
-  ctx->T.iw = ctx->d_tables + L * n;
+  set_ntt_loge(ctx, C.ntt_loge);
   // keys
   if (launch_keygen(ctx->d_s_ntt, ctx->d_s_coeff, ctx->d_pk_coeff, ctx->d_pk_ntt, C, ctx->T, nullptr) != hipSuccess ||
       hipDeviceSynchronize() != hipSuccess)
@@ -640,6 +681,11 @@ static View view_out(const pencil_layer* L, int op) {
   } else {  // dW [co][ci][kh][kw] with (m, r) = (ci, co)
     v.s0 = kh * kw; v.s1 = ci * kh * kw; v.sy = kw;
   }
+  return v;
+}
+
+static View stored(View v, int form) {
+  v.form = form;
   return v;
 }
 
@@ -943,6 +989,7 @@ static pencil_status run_product(pencil_ctx* ctx, const pencil_layer* L, int op,
   const int form_a = matrix ? FORM_DIGITS : FORM_SPLIT, form_k = matrix ? FORM_REVERSED : FORM_SPLIT;
   MacArgs A{};
   A.n_terms = n_terms;
+  A.matrix = matrix;
   A.m_rows = G.nM * G.nOY * G.nOX;
   A.variant = sched;
   A.pk = ctx->d_pk_split;
@@ -959,7 +1006,7 @@ static pencil_status run_product(pencil_ctx* ctx, const pencil_layer* L, int op,
       hipError_t e = hipSuccess;
       MacTerm mt{T.ct, pts, poly, 1, 0};
       if (add_share) {
-        e = timed(ctx, KID_NTT_CT, s, [&] { return launch_ntt_ct(T.ct, cts, form_a, na, add_share, G, view_a(L, op), C, ctx->T, s); });
+        e = timed(ctx, KID_NTT_CT, s, [&] { return launch_ntt_ct(T.ct, cts, na, add_share, G, stored(view_a(L, op), form_a), C, ctx->T, s); });
         if (matrix) {
           A.stage = cts;
         } else {
@@ -968,14 +1015,14 @@ static pencil_status run_product(pencil_ctx* ctx, const pencil_layer* L, int op,
         }
       }
       if (e == hipSuccess)
-        e = timed(ctx, KID_NTT_PT, s, [&] { return launch_ntt_pt(T.pt, pts, form_k, nk, 1, G, view_k(L, op), C, ctx->T, s); });
+        e = timed(ctx, KID_NTT_PT, s, [&] { return launch_ntt_pt(T.pt, pts, nk, 1, G, stored(view_k(L, op), form_k), C, ctx->T, s); });
       if (e != hipSuccess) return fail(ctx, PENCIL_EHIP, "ntt launch: %s", hipGetErrorString(e));
       A.term[i] = mt;
     } else {
       uint64_t* pts = w;
       w += na * poly;
       w += nk * ctw;
-      hipError_t e = timed(ctx, KID_NTT_PT, s, [&] { return launch_ntt_pt(T.pt, pts, form_a, na, 0, G, view_a(L, op), C, ctx->T, s); });
+      hipError_t e = timed(ctx, KID_NTT_PT, s, [&] { return launch_ntt_pt(T.pt, pts, na, 0, G, stored(view_a(L, op), form_a), C, ctx->T, s); });
       if (e != hipSuccess) return fail(ctx, PENCIL_EHIP, "ntt launch: %s", hipGetErrorString(e));
       A.term[i] = MacTerm{pts, T.ct, poly, 0, 0};
     }
@@ -984,9 +1031,7 @@ static pencil_status run_product(pencil_ctx* ctx, const pencil_layer* L, int op,
   const uint64_t obj = out_object(op, 0);
   hipError_t e = timed(ctx, KID_NTT_TERNARY, s, [&] { return launch_ntt_ternary(u, no, nonce, obj, P_RR_U, matrix ? FORM_BLOCKED_SPLIT : FORM_SPLIT, C, ctx->T, s); });
   A.u = u;
-  if (e == hipSuccess) e = timed(ctx, KID_MAC, s, [&] {
-      return matrix ? launch_mac_matrix(A, G, C, s) : launch_mac(A, no, G, C, s);
-    });
+  if (e == hipSuccess) e = timed(ctx, KID_MAC, s, [&] { return launch_mac(A, no, G, C, s); });
   if (e == hipSuccess) e = timed(ctx, KID_INTT_OUT, s, [&] { return launch_ntt_plain(ct_out, 2 * no, true, C, ctx->T, s); });
   if (e == hipSuccess)
     e = timed(ctx, KID_FLOOD, s, [&] {
@@ -1365,9 +1410,6 @@ extern "C" pencil_status pencil_stride_relayout(pencil_ctx* ctx, const pencil_la
 
 // ------------------------------------------------------------ batched step
 
-// Key of the matrix-core multiply-accumulate's phase (after the schedule kinds).
-constexpr int kMacMatrix = kMacVariants / 3;
-
 struct pencil_step {
   struct Entry {
     int ctx;
@@ -1385,7 +1427,7 @@ struct pencil_step {
   uint64_t* d_nonce = nullptr;
   struct Phase {
     int kind;  // 0 ntt, 1 mac, 2 intt, 3 flood
-    int key;   // NTT phases: 8 log2 N + log2(residues per thread); flood: words
+    int key;   // NTT phases: step_ntt_key; mac: kernel kind; flood: words
     std::vector<StepSeg> segs;
     StepSeg* d_segs = nullptr;
     int64_t blocks = 0;
@@ -1490,6 +1532,9 @@ extern "C" pencil_status pencil_step_workspace(const pencil_step* st, uint64_t* 
   return PENCIL_OK;
 }
 
+// Contexts whose transforms run as one launch: 16 log2 N + launch_step_ntt's width.
+static int step_ntt_key(const Consts& C) { return C.log2n * 16 + C.ntt_loge + (C.fold60 ? 8 : 0); }
+
 static pencil_step::Phase& phase_for(pencil_step* st, int kind, int key) {
   for (auto& ph : st->phases)
     if (ph.kind == kind && ph.key == key) return ph;
@@ -1553,9 +1598,9 @@ static pencil_status step_bind_tables(pencil_step* st, const pencil_step_io* io,
     for (auto& e : st->layers) {
       const Consts& C = st->ctxs[e.ctx]->C;
       if (kind == 1) {  // each multiply-accumulate kernel kind launches separately
-        for (int k = 0; k < kMacVariants / 3 + 1; ++k) phase_for(st, 1, k);
+        for (int k = 0; k <= kMacMatrix; ++k) phase_for(st, 1, k);
       } else {
-        phase_for(st, kind, kind == 3 ? C.flood_words : C.log2n * 8 + C.ntt_loge);
+        phase_for(st, kind, kind == 3 ? C.flood_words : step_ntt_key(C));
       }
     }
   for (size_t i = 0; i < st->layers.size(); ++i) {
@@ -1580,7 +1625,7 @@ static pencil_status step_bind_tables(pencil_step* st, const pencil_step_io* io,
         return step_fail(st, PENCIL_EINVAL, "missing buffer in step io");
       uint64_t* w = (uint64_t*)((uint8_t*)ws + e.ws_off[op]);
       const uint64_t nonce_off = 2 * (uint64_t)i + (op == 0 ? 0 : 1);
-      auto& ntt = phase_for(st, 0, C.log2n * 8 + C.ntt_loge);
+      auto& ntt = phase_for(st, 0, step_ntt_key(C));
       MacArgs A{};
       A.m_rows = G.nM * G.nOY * G.nOX;
       A.variant = e.P.sched[op];
@@ -1589,6 +1634,7 @@ static pencil_status step_bind_tables(pencil_step* st, const pencil_step_io* io,
       A.out = ct_out;
       const bool matrix = mac_use_matrix(C, op == 2 ? 2 : 1, A.m_rows, G);
       const int form_a = matrix ? FORM_DIGITS : FORM_SPLIT, form_k = matrix ? FORM_REVERSED : FORM_SPLIT;
+      A.matrix = matrix;
       StepSeg base{};
       base.ctx = e.ctx;
       base.G = G;
@@ -1607,8 +1653,7 @@ static pencil_status step_bind_tables(pencil_step* st, const pencil_step_io* io,
           sc.src = ct_a;
           sc.dst = cts;
           sc.tensor = add_share;
-          sc.V = view_a(L, op);
-          sc.form = form_a;
+          sc.V = stored(view_a(L, op), form_a);
           sc.count = na;
           add_seg(ntt, sc, na * C.L);
           if (matrix) {
@@ -1623,8 +1668,7 @@ static pencil_status step_bind_tables(pencil_step* st, const pencil_step_io* io,
         sp.side = 1;
         sp.tensor = pt_k;
         sp.dst = pts;
-        sp.V = view_k(L, op);
-        sp.form = form_k;
+        sp.V = stored(view_k(L, op), form_k);
         sp.count = nk;
         add_seg(ntt, sp, nk * C.L);
         A.term[0] = mt;
@@ -1639,8 +1683,7 @@ static pencil_status step_bind_tables(pencil_step* st, const pencil_step_io* io,
         sp.side = 0;
         sp.tensor = b.x0;
         sp.dst = pts;
-        sp.V = view_a(L, op);
-        sp.form = form_a;
+        sp.V = stored(view_a(L, op), form_a);
         sp.count = na;
         add_seg(ntt, sp, na * C.L);
         A.term[1] = MacTerm{pts, b.ct_dy_dw, poly, 0, 0};
@@ -1653,7 +1696,7 @@ static pencil_status step_bind_tables(pencil_step* st, const pencil_step_io* io,
       su.nonce_off = nonce_off;
       su.obj_base = out_object(op, 0);
       su.purpose = P_RR_U;
-      su.form = matrix ? FORM_BLOCKED_SPLIT : FORM_SPLIT;
+      su.V.form = matrix ? FORM_BLOCKED_SPLIT : FORM_SPLIT;
       su.count = no;
       add_seg(ntt, su, no * C.L);
       A.u = u;
@@ -1668,7 +1711,7 @@ static pencil_status step_bind_tables(pencil_step* st, const pencil_step_io* io,
       StepSeg si = base;
       si.kind = SEG_INTT;
       si.dst = ct_out;
-      add_seg(phase_for(st, 2, C.log2n * 8 + C.ntt_loge), si, 2 * no * C.L);
+      add_seg(phase_for(st, 2, step_ntt_key(C)), si, 2 * no * C.L);
       StepSeg sf = base;
       sf.kind = SEG_FLOOD;
       sf.dst = ct_out;
@@ -1705,11 +1748,9 @@ static hipError_t step_phases(pencil_step* st, hipStream_t s) {
     pencil_ctx* pc = st->ctxs[0];
     if (ph.kind == 0 || ph.kind == 2)
       e = timed(pc, ph.kind == 0 ? KID_STEP_NTT : KID_STEP_INTT, s,
-                [&] { return launch_step_ntt(ph.key / 8, ph.key % 8, ph.kind == 2, P, ph.blocks, s); });
+                [&] { return launch_step_ntt(ph.key / 16, ph.key % 16, ph.kind == 2, P, ph.blocks, s); });
     else if (ph.kind == 1)
-      e = timed(pc, KID_STEP_MAC, s, [&] { 
-        return ph.key == kMacMatrix ? launch_step_mac_matrix(P, ph.blocks, s) : launch_step_mac(P, ph.blocks, ph.key, s);
-      });
+      e = timed(pc, KID_STEP_MAC, s, [&] {  return launch_step_mac(P, ph.blocks, ph.key, s); });
     else
       e = timed(pc, KID_STEP_FLOOD, s, [&] { return launch_step_flood(ph.key, P, ph.blocks, s); });
     if (e != hipSuccess) return e;
@@ -1971,14 +2012,14 @@ extern "C" pencil_status pencil_autotune(pencil_ctx* ctx, const pencil_layer* L,
   std::snprintf(key, sizeof key, "%s N=%d L=%d ntt_loge", arch.c_str(), C.n, C.L);
   if (const std::vector<int>* hit = cache_find(cache, key)) {
     if (hit->size() == 1 && (*hit)[0] >= 4 && (*hit)[0] <= 5 && (C.log2n >= 12 || (*hit)[0] == 4))
-      C.ntt_loge = (*hit)[0];
+      set_ntt_loge(ctx, (*hit)[0]);
   } else {
     std::vector<int> cands = C.log2n >= 12 ? std::vector<int>{4, 5} : std::vector<int>{4};
     std::vector<float> times;
     int bestv = C.ntt_loge;
     float best = -1;
     for (int c : cands) {
-      C.ntt_loge = c;
+      set_ntt_loge(ctx, c);
       const float ms = step_ms(P);
       times.push_back(ms);
       if (ms > 0 && (best < 0 || ms < best)) {
@@ -1986,7 +2027,7 @@ extern "C" pencil_status pencil_autotune(pencil_ctx* ctx, const pencil_layer* L,
         bestv = c;
       }
     }
-    C.ntt_loge = bestv;
+    set_ntt_loge(ctx, bestv);
     fresh.push_back(std::string("{\"key\": \"") + key + "\", \"choice\": " + std::to_string(bestv) +
                     ", \"candidates\": [4, 5], \"ms\": [" + times_str(times) + "]}");
   }

@@ -8,7 +8,7 @@ namespace pencil {
 // c = 0)), with m the encoded share at each slot, each residue stored in the
 // multiply-accumulate's split form; the product path consumes ciphertexts in
 // this form.  Grid: n_ct * 2 * L, u_ntt is [n][L][N].
-template <int LOGN, int LOGE>
+template <int LOGN, int LOGE, bool F60>
 __global__ void PENCIL_NTT_BOUNDS(LOGN, LOGE) k_encrypt(const uint64_t* u_ntt, const int64_t* share, uint64_t* ct, int side,
                                                   Geo G, View V, const uint64_t* pk_ntt, const uint64_t* pk_sh,
                                                   uint64_t nonce, uint64_t obj_base, Consts C, Tables T) {
@@ -42,14 +42,14 @@ __global__ void PENCIL_NTT_BOUNDS(LOGN, LOGE) k_encrypt(const uint64_t* u_ntt, c
     }
   }
   __syncthreads();
-  ntt_fwd<LOGN, LOGE>(lds, T.fw + (int64_t)l * n, lc.q);
+  ntt_fwd<LOGN, LOGE, F60>(lds, T.fw + (int64_t)l * n, lc.q);
   uint64_t* o = ct + p * n;
   for (int i = threadIdx.x; i < n; i += blockDim.x)
     o[i] = split30(add_mod(mul_shoup(u[i], pk[i], pks[i], lc.q), lds[lpad(i)], lc.q));
 }
 
 // Decryption phase per limb: x = c0 + INTT(NTT(c1) * s).  Grid: n * L, x is [n][L][N].
-template <int LOGN, int LOGE>
+template <int LOGN, int LOGE, bool F60>
 __global__ void PENCIL_NTT_BOUNDS(LOGN, LOGE) k_phase(const uint64_t* ct, uint64_t* x, const uint64_t* s_ntt,
                                                 const uint64_t* s_sh, Consts C, Tables T) {
   extern __shared__ uint64_t lds[];
@@ -63,15 +63,16 @@ __global__ void PENCIL_NTT_BOUNDS(LOGN, LOGE) k_phase(const uint64_t* ct, uint64
   const uint64_t* c1 = ct + ((j * 2 + 1) * L + l) * n;
   for (int i = threadIdx.x; i < n; i += blockDim.x) lds[lpad(i)] = c1[i];
   __syncthreads();
-  ntt_fwd<LOGN, LOGE>(lds, T.fw + (int64_t)l * n, lc.q);
+  ntt_fwd<LOGN, LOGE, F60>(lds, T.fw + (int64_t)l * n, lc.q);
   const uint64_t* sv = s_ntt + (int64_t)l * n;
   const uint64_t* ss = s_sh + (int64_t)l * n;
   for (int i = threadIdx.x; i < n; i += blockDim.x) lds[lpad(i)] = mul_shoup(lds[lpad(i)], sv[i], ss[i], lc.q);
   __syncthreads();
-  ntt_inv<LOGN, LOGE>(lds, T.iw + (int64_t)l * n, lc.q);
   uint64_t* o = x + p * n;
-  for (int i = threadIdx.x; i < n; i += blockDim.x)
-    o[i] = add_mod(c0[i], mul_shoup(lds[lpad(i)], lc.ninv, lc.ninv_sh, lc.q), lc.q);
+  uint64_t* poly = lds;
+  ntt_inv_in<LOGN, LOGE, F60>(
+      lds, [poly](int i) { return poly[lpad(i)]; },
+      [o, c0, &lc](int i, uint64_t v) { o[i] = add_mod(c0[i], v, lc.q); }, T.iw + (int64_t)l * n, lc.q);
 }
 
 // Exact decryption of the output slots: with y_l = x_l * (q/q_l)^-1 mod q_l and
@@ -173,7 +174,7 @@ __global__ void __launch_bounds__(256) k_decode(const uint64_t* x, int64_t* shar
 // (stream P_PK_A, limb l, two words per coefficient), e CBD21 (stream P_PK_E);
 // pk = (-(a s + e), a), kept in both coefficient and NTT form.  One LDS buffer;
 // every thread re-reads only the global entries it wrote itself.
-template <int LOGN, int LOGE>
+template <int LOGN, int LOGE, bool F60>
 __global__ void PENCIL_NTT_BOUNDS(LOGN, LOGE) k_keygen(uint64_t* s_ntt, int64_t* s_coeff, uint64_t* pk_coeff,
                                                  uint64_t* pk_ntt, Consts C, Tables T) {
   extern __shared__ uint64_t lds[];
@@ -193,7 +194,7 @@ __global__ void PENCIL_NTT_BOUNDS(LOGN, LOGE) k_keygen(uint64_t* s_ntt, int64_t*
     }
   }
   __syncthreads();
-  ntt_fwd<LOGN, LOGE>(lds, tw, lc.q);
+  ntt_fwd<LOGN, LOGE, F60>(lds, tw, lc.q);
   for (int i = threadIdx.x; i < n; i += blockDim.x) s_ntt[(int64_t)l * n + i] = lds[lpad(i)];
   __syncthreads();
   for (int blk = threadIdx.x; blk < n / 2; blk += blockDim.x) {
@@ -208,7 +209,7 @@ __global__ void PENCIL_NTT_BOUNDS(LOGN, LOGE) k_keygen(uint64_t* s_ntt, int64_t*
     }
   }
   __syncthreads();
-  ntt_fwd<LOGN, LOGE>(lds, tw, lc.q);
+  ntt_fwd<LOGN, LOGE, F60>(lds, tw, lc.q);
   // a * s pointwise (128-bit product, Barrett), then inverse transform
   for (int i = threadIdx.x; i < n; i += blockDim.x) {
     const uint64_t av = lds[lpad(i)];
@@ -218,13 +219,14 @@ __global__ void PENCIL_NTT_BOUNDS(LOGN, LOGE) k_keygen(uint64_t* s_ntt, int64_t*
     lds[lpad(i)] = reduce128(ph, pl, lc.q, lc.mu_lo, lc.mu_hi);
   }
   __syncthreads();
-  ntt_inv<LOGN, LOGE>(lds, T.iw + (int64_t)l * n, lc.q);
+  ntt_inv<LOGN, LOGE, F60>(lds, T.iw + (int64_t)l * n, lc.q);
+  __syncthreads();
   for (int blk = threadIdx.x; blk < n / 4; blk += blockDim.x) {
     U64x4 w = philox((uint64_t)blk, 0, P_PK_E, 0, C.seed, nonce);
 #pragma unroll
     for (int z = 0; z < 4; ++z) {
       const int i = blk * 4 + z;
-      uint64_t as = mul_shoup(lds[lpad(i)], lc.ninv, lc.ninv_sh, lc.q);
+      uint64_t as = lds[lpad(i)];
       uint64_t v = add_mod(as, small_to_mod(cbd21(w.v[z]), lc.q), lc.q);
       v = v == 0 ? 0 : lc.q - v;
       lds[lpad(i)] = v;
@@ -232,7 +234,7 @@ __global__ void PENCIL_NTT_BOUNDS(LOGN, LOGE) k_keygen(uint64_t* s_ntt, int64_t*
     }
   }
   __syncthreads();
-  ntt_fwd<LOGN, LOGE>(lds, tw, lc.q);
+  ntt_fwd<LOGN, LOGE, F60>(lds, tw, lc.q);
   for (int i = threadIdx.x; i < n; i += blockDim.x) pk_ntt[(int64_t)l * n + i] = lds[lpad(i)];
 }
 
@@ -272,16 +274,20 @@ hipError_t launch_keygen(uint64_t* s_ntt, int64_t* s_coeff, uint64_t* pk_coeff, 
 hipError_t configure_lds_do() {
   const int max_lds = 160 * 1024;
   hipError_t e = hipSuccess;
-#define PENCIL_RAISE(LN, LE)                                                                            \
-  for (const void* f : {(const void*)k_encrypt<LN, LE>, (const void*)k_phase<LN, LE>,                    \
-                        (const void*)k_keygen<LN, LE>}) {                                                \
+#define PENCIL_RAISE(LN, LE, F)                                                                            \
+  for (const void* f : {(const void*)k_encrypt<LN, LE, F>, (const void*)k_phase<LN, LE, F>,                    \
+                        (const void*)k_keygen<LN, LE, F>}) {                                                \
     hipError_t r = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, max_lds);         \
     if (r != hipSuccess) e = r;                                                                          \
   }
-  PENCIL_RAISE(13, 4)
-  PENCIL_RAISE(13, 5)
-  PENCIL_RAISE(14, 4)
-  PENCIL_RAISE(14, 5)
+  PENCIL_RAISE(13, 4, false)
+  PENCIL_RAISE(13, 4, true)
+  PENCIL_RAISE(13, 5, false)
+  PENCIL_RAISE(13, 5, true)
+  PENCIL_RAISE(14, 4, false)
+  PENCIL_RAISE(14, 4, true)
+  PENCIL_RAISE(14, 5, false)
+  PENCIL_RAISE(14, 5, true)
 #undef PENCIL_RAISE
   return e;
 }

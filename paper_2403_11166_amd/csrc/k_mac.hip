@@ -696,6 +696,7 @@ hipError_t launch_mac(const MacArgs& A, int64_t n_out, const Geo& G, const Const
   const int chunks = mac_chunks(A.variant, A.m_rows, G.nR);
   const int64_t total = slot_blocks * chunks;
   if (total >= (1ll << 31)) return hipErrorInvalidConfiguration;  // work items are int
+  if (A.matrix) return launch_mac_matrix(A, G, C, s);
   if (A.variant >= 6)
     hipLaunchKernelGGL(k_mac_direct_small, dim3((unsigned)total), dim3(512), 0, s, A, G, C, chunks, total);
   else if (A.variant >= 3)
@@ -708,6 +709,7 @@ hipError_t launch_mac(const MacArgs& A, int64_t n_out, const Geo& G, const Const
 
 hipError_t launch_step_mac(const StepPhase& P, int64_t blocks, int kind, hipStream_t s) {
   if (blocks <= 0) return hipSuccess;
+  if (kind == kMacMatrix) return launch_step_mac_matrix(P, blocks, s);
   if (kind == 2)
     hipLaunchKernelGGL(k_step_mac_direct_small, dim3((unsigned)blocks), dim3(512), 0, s, P.segs, P.nseg, P.consts);
   else if (kind == 1)

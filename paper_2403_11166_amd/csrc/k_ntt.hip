@@ -4,31 +4,30 @@
 
 namespace pencil {
 
-template <int LOGN, int LOGE>
+template <int LOGN, int LOGE, bool F60>
 __global__ void PENCIL_NTT_BOUNDS(LOGN, LOGE) k_ntt_plain(uint64_t* data, int inverse, Consts C, Tables T) {
   extern __shared__ uint64_t lds[];
-  do_ntt_plain<LOGN, LOGE>(lds, data, inverse, C, T, blockIdx.x);
+  do_ntt_plain<LOGN, LOGE, F60>(lds, data, inverse, C, T, blockIdx.x);
 }
 
-template <int LOGN, int LOGE>
-__global__ void PENCIL_NTT_BOUNDS(LOGN, LOGE) k_ntt_ct(const uint64_t* src, uint64_t* dst, int form, int64_t count,
+template <int LOGN, int LOGE, bool F60>
+__global__ void PENCIL_NTT_BOUNDS(LOGN, LOGE) k_ntt_ct(const uint64_t* src, uint64_t* dst, int64_t count,
                                                        const int64_t* share, Geo G, View V, Consts C, Tables T) {
   extern __shared__ uint64_t lds[];
-  do_ntt_ct<LOGN, LOGE>(lds, src, dst, form, count, share, G, V, C, T, blockIdx.x);
+  do_ntt_ct<LOGN, LOGE, F60>(lds, src, dst, count, share, G, V, C, T, blockIdx.x);
 }
 
-template <int LOGN, int LOGE>
-__global__ void PENCIL_NTT_BOUNDS(LOGN, LOGE) k_ntt_pt(const int64_t* tensor, uint64_t* dst, int form, int64_t count,
-                                                       int side, Geo G, View V, Consts C, Tables T) {
+template <int LOGN, int LOGE, bool F60>
+__global__ void PENCIL_NTT_BOUNDS(LOGN, LOGE) k_ntt_pt(const int64_t* tensor, uint64_t* dst, int64_t count, int side, Geo G, View V, Consts C, Tables T) {
   extern __shared__ uint64_t lds[];
-  do_ntt_pt<LOGN, LOGE>(lds, tensor, dst, form, count, side, G, V, C, T, blockIdx.x);
+  do_ntt_pt<LOGN, LOGE, F60>(lds, tensor, dst, count, side, G, V, C, T, blockIdx.x);
 }
 
-template <int LOGN, int LOGE>
+template <int LOGN, int LOGE, bool F60>
 __global__ void PENCIL_NTT_BOUNDS(LOGN, LOGE) k_ntt_ternary(uint64_t* dst, uint64_t nonce, uint64_t obj_base,
                                                       uint32_t purpose, int form, int64_t count, Consts C, Tables T) {
   extern __shared__ uint64_t lds[];
-  do_ntt_ternary<LOGN, LOGE>(lds, dst, nonce, obj_base, purpose, form, count, C, T, blockIdx.x);
+  do_ntt_ternary<LOGN, LOGE, F60>(lds, dst, nonce, obj_base, purpose, form, count, C, T, blockIdx.x);
 }
 
 hipError_t launch_ntt_plain(uint64_t* data, int64_t polys, bool inverse, const Consts& C, const Tables& T,
@@ -38,17 +37,17 @@ hipError_t launch_ntt_plain(uint64_t* data, int64_t polys, bool inverse, const C
   return hipGetLastError();
 }
 
-hipError_t launch_ntt_ct(const uint64_t* src, uint64_t* dst, int form, int64_t n_ct, const int64_t* share, const Geo& G,
+hipError_t launch_ntt_ct(const uint64_t* src, uint64_t* dst, int64_t n_ct, const int64_t* share, const Geo& G,
                          const View& V, const Consts& C, const Tables& T, hipStream_t s) {
   if (n_ct <= 0) return hipSuccess;
-  NTT_DISPATCH(k_ntt_ct, dim3((unsigned)(n_ct * C.L)), C, s, src, dst, form, n_ct, share, G, V, C, T);
+  NTT_DISPATCH(k_ntt_ct, dim3((unsigned)(n_ct * C.L)), C, s, src, dst, n_ct, share, G, V, C, T);
   return hipGetLastError();
 }
 
-hipError_t launch_ntt_pt(const int64_t* tensor, uint64_t* dst, int form, int64_t n_pt, int side, const Geo& G, const View& V,
+hipError_t launch_ntt_pt(const int64_t* tensor, uint64_t* dst, int64_t n_pt, int side, const Geo& G, const View& V,
                          const Consts& C, const Tables& T, hipStream_t s) {
   if (n_pt <= 0) return hipSuccess;
-  NTT_DISPATCH(k_ntt_pt, dim3((unsigned)(n_pt * C.L)), C, s, tensor, dst, form, n_pt, side, G, V, C, T);
+  NTT_DISPATCH(k_ntt_pt, dim3((unsigned)(n_pt * C.L)), C, s, tensor, dst, n_pt, side, G, V, C, T);
   return hipGetLastError();
 }
 
@@ -62,16 +61,20 @@ hipError_t launch_ntt_ternary(uint64_t* dst, int64_t count, uint64_t nonce, uint
 hipError_t configure_lds_ntt() {
   const int max_lds = 160 * 1024;
   hipError_t e = hipSuccess;
-#define PENCIL_RAISE(LN, LE)                                                                            \
-  for (const void* f : {(const void*)k_ntt_plain<LN, LE>, (const void*)k_ntt_ct<LN, LE>,                 \
-                        (const void*)k_ntt_pt<LN, LE>, (const void*)k_ntt_ternary<LN, LE>}) {            \
+#define PENCIL_RAISE(LN, LE, F)                                                                            \
+  for (const void* f : {(const void*)k_ntt_plain<LN, LE, F>, (const void*)k_ntt_ct<LN, LE, F>,                 \
+                        (const void*)k_ntt_pt<LN, LE, F>, (const void*)k_ntt_ternary<LN, LE, F>}) {            \
     hipError_t r = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, max_lds);         \
     if (r != hipSuccess) e = r;                                                                          \
   }
-  PENCIL_RAISE(13, 4)
-  PENCIL_RAISE(13, 5)
-  PENCIL_RAISE(14, 4)
-  PENCIL_RAISE(14, 5)
+  PENCIL_RAISE(13, 4, false)
+  PENCIL_RAISE(13, 4, true)
+  PENCIL_RAISE(13, 5, false)
+  PENCIL_RAISE(13, 5, true)
+  PENCIL_RAISE(14, 4, false)
+  PENCIL_RAISE(14, 4, true)
+  PENCIL_RAISE(14, 5, false)
+  PENCIL_RAISE(14, 5, true)
 #undef PENCIL_RAISE
   return e;
 }

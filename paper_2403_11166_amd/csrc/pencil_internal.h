@@ -18,7 +18,6 @@ struct LimbConst {
   uint64_t r64_split, r96_split, mx_off;
   uint32_t delta60, pad0;
   uint64_t one_sh;               // floor(2^64 / q)
-  uint64_t ninv, ninv_sh;        // N^-1 mod q
   uint64_t delta, delta_sh;      // floor(q / t) mod q_l
   uint64_t t_sh;                 // floor(t * 2^64 / q_l), t < q_l
   uint64_t qhat_inv, qhat_inv_sh;// ((q / q_l)^-1) mod q_l
@@ -44,12 +43,26 @@ struct Consts {
   uint64_t thr[kMaxLimbs][kMaxWords];   // (2j + 1) * q, j = 0..L-1
 };
 
-// A twiddle and its Shoup companion, stored together for one 16-byte load.
+// A twiddle w and its companion, stored together for one 16-byte load: w and
+// floor(w 2^64 / q), or for contexts with fold60 the split forms of w and of
+// w 2^32 mod q.
 struct alignas(16) TW {
   uint64_t w, ws;
 };
 
-// NTT tables, each [L][N]: psi^rev(k) (forward) and psi^-rev(k) (inverse).
+// Stages of pass i of a transform (the first log2 N mod NP of its NP =
+// ceil(log2 N / loge) passes take one more), and how many precede it.
+__host__ __device__ constexpr int ntt_pass_count(int logn, int loge) { return (logn + loge - 1) / loge; }
+__host__ __device__ constexpr int ntt_pass_size(int logn, int loge, int i) {
+  return logn / ntt_pass_count(logn, loge) + (i < logn % ntt_pass_count(logn, loge) ? 1 : 0);
+}
+__host__ __device__ constexpr int ntt_pass_start(int logn, int loge, int i) {
+  return i == 0 ? 0 : ntt_pass_start(logn, loge, i - 1) + ntt_pass_size(logn, loge, i - 1);
+}
+
+// NTT tables, each [L][N]: psi^rev(k) (forward) and psi^-rev(k) (inverse), in the
+// order in which the passes of the context's ntt_loge read them (twiddle_at);
+// entries 0 and 1 of the inverse table hold N^-1 and N^-1 psi^-rev(1).
 struct Tables {
   const TW* fw;
   const TW* iw;
@@ -71,13 +84,19 @@ struct Geo {
   uint32_t dv_kw, dv_khw, dv_kthw, dv_sp;  // sp = nOY nOX
 };
 
+// Slots per group of the slot-blocked buffers (a 512-byte run), and the forms
+// the forward transforms write (form_value, store_form).
+constexpr int kMxGroup = 64;
+enum Form : int32_t { FORM_PLAIN = 0, FORM_SPLIT = 1, FORM_DIGITS = 2, FORM_REVERSED = 3, FORM_BLOCKED_SPLIT = 4 };
+
 // Maps virtual coordinates (i0, i1, y, x) of an operand to an element offset of
 // the caller's tensor.  A side: y, x are shifted by -pad and bounded by H, W.
 // K side: flip mirrors the kernel window.  Output: plain strides.
 struct View {
   int64_t s0, s1, sy, sx;
   int32_t pad, H, W, flip;   // pad: zero columns before the tensor (and rows, see pady)
-  int32_t KH, KW, pady, pad3;
+  int32_t KH, KW, pady;
+  int32_t form;              // how the forward transform stores the operand's polynomials (Form)
 };
 
 // Philox stream purposes.
@@ -91,11 +110,6 @@ constexpr uint64_t kKeygenNonce = ~0ull;
 
 inline uint64_t enc_object(int operand, uint64_t i) { return ((uint64_t)(operand + 1) << 48) | i; }
 inline uint64_t out_object(int op, uint64_t i) { return ((uint64_t)(op + 5) << 48) | i; }
-
-// Slots per group of the slot-blocked buffers (a 512-byte run), and the forms
-// the forward transforms write (form_value, store_form).
-constexpr int kMxGroup = 64;
-enum Form : int32_t { FORM_PLAIN = 0, FORM_SPLIT = 1, FORM_DIGITS = 2, FORM_REVERSED = 3, FORM_BLOCKED_SPLIT = 4 };
 
 // One term of a product: which side holds the ciphertext and where both operands live
 // (NTT domain, split form).  ct: [n][2][L][N] (component 0 addresses); pt: [n][L][N].
@@ -115,7 +129,7 @@ struct MacArgs {
   int32_t n_terms;
   int32_t m_rows;      // nM * nOY * nOX
   int32_t variant;     // multiply-accumulate schedule (0..kMacVariants-1), see mac_rows
-  int32_t pad;
+  int32_t matrix;      // 1: on the matrix cores (operands slot-blocked, in digits)
   const uint64_t* pk;  // [2][L][N], NTT domain, split form
   const uint64_t* u;   // [n_out][L][N], NTT domain (slot-blocked for the matrix cores)
   const uint64_t* stage;  // matrix cores: component 0 of term 0 with the share added, or null
@@ -129,7 +143,7 @@ enum SegKind : int32_t { SEG_CT = 0, SEG_PT = 1, SEG_TERN = 2, SEG_INTT = 3, SEG
 
 struct StepSeg {
   int64_t block_begin;       // first block of the segment in its phase grid
-  int32_t kind, ctx, side, purpose, form, pad;
+  int32_t kind, ctx, side, purpose;
   int64_t count;             // flood: output ciphertexts; forward NTTs: tiles of the operand
   int64_t slot_blocks;       // mac: 64-slot groups (work items = slot_blocks x chunks)
   uint64_t nonce_off, obj_base;
@@ -159,6 +173,7 @@ struct StepPhase {
 // chunk (A rows x K rows) of the block's 8 waves: 4 x 8, 2 x 16, 8 x 4
 // (kinds 0, 1) or 4 x 4, 2 x 8, 8 x 2 (kind 2).
 constexpr int kMacVariants = 9;
+constexpr int kMacMatrix = kMacVariants / 3;  // kind of the matrix-core kernel, after the schedules' kinds
 __host__ __device__ inline int mac_rows(int variant) { return variant % 3 == 1 ? 2 : variant % 3 == 2 ? 8 : 4; }
 __host__ __device__ inline int mac_cols(int variant) {
   const int c = variant % 3 == 1 ? 16 : variant % 3 == 2 ? 4 : 8;
@@ -182,9 +197,9 @@ __host__ __device__ inline int64_t mac_matrix_groups(int n, int limbs) { return 
 // (defined in kernels.hip; all enqueue on `stream` and return the launch status)
 hipError_t launch_ntt_plain(uint64_t* data, int64_t polys, bool inverse, const Consts& C, const Tables& T,
                             hipStream_t s);
-hipError_t launch_ntt_ct(const uint64_t* src, uint64_t* dst, int form, int64_t n_ct, const int64_t* share, const Geo& G,
+hipError_t launch_ntt_ct(const uint64_t* src, uint64_t* dst, int64_t n_ct, const int64_t* share, const Geo& G,
                          const View& V, const Consts& C, const Tables& T, hipStream_t s);
-hipError_t launch_ntt_pt(const int64_t* tensor, uint64_t* dst, int form, int64_t n_pt, int side, const Geo& G, const View& V,
+hipError_t launch_ntt_pt(const int64_t* tensor, uint64_t* dst, int64_t n_pt, int side, const Geo& G, const View& V,
                          const Consts& C, const Tables& T, hipStream_t s);
 hipError_t launch_ntt_ternary(uint64_t* dst, int64_t count, uint64_t nonce, uint64_t obj_base, uint32_t purpose, int form,
                               const Consts& C, const Tables& T, hipStream_t s);
@@ -225,7 +240,8 @@ struct Relayout {
 hipError_t launch_stride_relayout(const Relayout& R, const int64_t* in, int64_t* out, hipStream_t s);
 hipError_t launch_zt_corr(const int64_t* a, const int64_t* k, int64_t* out, const Geo& G, const View& AV,
                           const View& KV, const View& OV, const Consts& C, hipStream_t s);
-hipError_t launch_step_ntt(int log2n, int loge, bool inverse, const StepPhase& P, int64_t blocks, hipStream_t s);
+// width: ntt_loge, plus 8 for contexts with fold60
+hipError_t launch_step_ntt(int log2n, int width, bool inverse, const StepPhase& P, int64_t blocks, hipStream_t s);
 hipError_t launch_step_mac(const StepPhase& P, int64_t blocks, int kind, hipStream_t s);
 hipError_t launch_step_mac_matrix(const StepPhase& P, int64_t blocks, hipStream_t s);
 hipError_t launch_step_flood(int words, const StepPhase& P, int64_t blocks, hipStream_t s);
