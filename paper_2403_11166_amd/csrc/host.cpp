@@ -935,6 +935,9 @@ extern "C" pencil_status pencil_encrypt(pencil_ctx* ctx, const pencil_layer* L, 
   return PENCIL_OK;
 }
 
+// Contexts whose transforms run as one launch: 16 log2 N + launch_step_ntt's width.
+static int step_ntt_key(const Consts& C) { return C.log2n * 16 + C.ntt_loge + (C.fold60 ? 8 : 0); }
+
 // Whether a product's multiply-accumulate runs on the matrix cores
 // (k_macx.hip).  First what that kernel's index arithmetic takes: contraction
 // sums within int32, reciprocal divisions of rows, evenly spaced tiles along the
@@ -994,6 +997,20 @@ static pencil_status run_product(pencil_ctx* ctx, const pencil_layer* L, int op,
   A.variant = sched;
   A.pk = ctx->d_pk_split;
   A.out = ct_out;
+  // every forward transform as one launch
+  NttCall N{};
+  int64_t blocks = 0;
+  int nseg = 0;
+  auto add = [&](int kind, int64_t count, uint64_t* dst, const View& V) -> NttSeg& {
+    NttSeg& g = N.seg[nseg++];
+    g.kind = kind;
+    g.count = count;
+    g.dst = dst;
+    g.V = V;
+    blocks += count * C.L;
+    g.block_end = blocks;
+    return g;
+  };
   for (int i = 0; i < n_terms; ++i) {
     const TermIn& T = terms[i];
     if (T.a_is_ct) {
@@ -1003,10 +1020,11 @@ static pencil_status run_product(pencil_ctx* ctx, const pencil_layer* L, int op,
       w += na * ctw;
       uint64_t* pts = w;
       w += nk * poly;
-      hipError_t e = hipSuccess;
       MacTerm mt{T.ct, pts, poly, 1, 0};
       if (add_share) {
-        e = timed(ctx, KID_NTT_CT, s, [&] { return launch_ntt_ct(T.ct, cts, na, add_share, G, stored(view_a(L, op), form_a), C, ctx->T, s); });
+        NttSeg& g = add(SEG_CT, na, cts, stored(view_a(L, op), form_a));
+        g.src = T.ct;
+        g.tensor = add_share;
         if (matrix) {
           A.stage = cts;
         } else {
@@ -1014,23 +1032,36 @@ static pencil_status run_product(pencil_ctx* ctx, const pencil_layer* L, int op,
           mt.c1 = comp1_offset(cts, T.ct, poly);
         }
       }
-      if (e == hipSuccess)
-        e = timed(ctx, KID_NTT_PT, s, [&] { return launch_ntt_pt(T.pt, pts, nk, 1, G, stored(view_k(L, op), form_k), C, ctx->T, s); });
-      if (e != hipSuccess) return fail(ctx, PENCIL_EHIP, "ntt launch: %s", hipGetErrorString(e));
+      NttSeg& g = add(SEG_PT, nk, pts, stored(view_k(L, op), form_k));
+      g.side = 1;
+      g.tensor = T.pt;
       A.term[i] = mt;
     } else {
       uint64_t* pts = w;
       w += na * poly;
       w += nk * ctw;
-      hipError_t e = timed(ctx, KID_NTT_PT, s, [&] { return launch_ntt_pt(T.pt, pts, na, 0, G, stored(view_a(L, op), form_a), C, ctx->T, s); });
-      if (e != hipSuccess) return fail(ctx, PENCIL_EHIP, "ntt launch: %s", hipGetErrorString(e));
+      NttSeg& g = add(SEG_PT, na, pts, stored(view_a(L, op), form_a));
+      g.tensor = T.pt;
       A.term[i] = MacTerm{pts, T.ct, poly, 0, 0};
     }
   }
   uint64_t* u = w;
   const uint64_t obj = out_object(op, 0);
-  hipError_t e = timed(ctx, KID_NTT_TERNARY, s, [&] { return launch_ntt_ternary(u, no, nonce, obj, P_RR_U, matrix ? FORM_BLOCKED_SPLIT : FORM_SPLIT, C, ctx->T, s); });
+  NttSeg& tern = add(SEG_TERN, no, u, stored(View{}, matrix ? FORM_BLOCKED_SPLIT : FORM_SPLIT));
+  tern.obj_base = obj;
+  tern.purpose = P_RR_U;
   A.u = u;
+  for (; nseg < kNttSegs; ++nseg) N.seg[nseg].block_end = blocks;
+  N.G = G;
+  N.C = C;
+  N.T = ctx->T;
+  N.nonce = nonce;
+  StepPhase P{};
+  P.call = &N;
+  if (blocks >= (1ll << 31)) return fail(ctx, PENCIL_EUNSUPPORTED, "too many input tiles for one launch");
+  hipError_t e = timed(ctx, KID_STEP_NTT, s, [&] {
+    return launch_step_ntt(C.log2n, step_ntt_key(C) % 16, false, P, blocks, s);
+  });
   if (e == hipSuccess) e = timed(ctx, KID_MAC, s, [&] { return launch_mac(A, no, G, C, s); });
   if (e == hipSuccess) e = timed(ctx, KID_INTT_OUT, s, [&] { return launch_ntt_plain(ct_out, 2 * no, true, C, ctx->T, s); });
   if (e == hipSuccess)
@@ -1531,9 +1562,6 @@ extern "C" pencil_status pencil_step_workspace(const pencil_step* st, uint64_t* 
   *bytes = st->ws_bytes;
   return PENCIL_OK;
 }
-
-// Contexts whose transforms run as one launch: 16 log2 N + launch_step_ntt's width.
-static int step_ntt_key(const Consts& C) { return C.log2n * 16 + C.ntt_loge + (C.fold60 ? 8 : 0); }
 
 static pencil_step::Phase& phase_for(pencil_step* st, int kind, int key) {
   for (auto& ph : st->phases)

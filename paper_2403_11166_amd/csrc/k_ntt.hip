@@ -1,5 +1,4 @@
-// Per-call NTT kernels: plain transforms and the forward-transform front ends
-// of one product.
+// Per-call NTT kernels: plain transforms and ternary polynomials.
 #include "ntt_core.h"
 
 namespace pencil {
@@ -8,19 +7,6 @@ template <int LOGN, int LOGE, bool F60>
 __global__ void PENCIL_NTT_BOUNDS(LOGN, LOGE) k_ntt_plain(uint64_t* data, int inverse, Consts C, Tables T) {
   extern __shared__ uint64_t lds[];
   do_ntt_plain<LOGN, LOGE, F60>(lds, data, inverse, C, T, blockIdx.x);
-}
-
-template <int LOGN, int LOGE, bool F60>
-__global__ void PENCIL_NTT_BOUNDS(LOGN, LOGE) k_ntt_ct(const uint64_t* src, uint64_t* dst, int64_t count,
-                                                       const int64_t* share, Geo G, View V, Consts C, Tables T) {
-  extern __shared__ uint64_t lds[];
-  do_ntt_ct<LOGN, LOGE, F60>(lds, src, dst, count, share, G, V, C, T, blockIdx.x);
-}
-
-template <int LOGN, int LOGE, bool F60>
-__global__ void PENCIL_NTT_BOUNDS(LOGN, LOGE) k_ntt_pt(const int64_t* tensor, uint64_t* dst, int64_t count, int side, Geo G, View V, Consts C, Tables T) {
-  extern __shared__ uint64_t lds[];
-  do_ntt_pt<LOGN, LOGE, F60>(lds, tensor, dst, count, side, G, V, C, T, blockIdx.x);
 }
 
 template <int LOGN, int LOGE, bool F60>
@@ -37,20 +23,6 @@ hipError_t launch_ntt_plain(uint64_t* data, int64_t polys, bool inverse, const C
   return hipGetLastError();
 }
 
-hipError_t launch_ntt_ct(const uint64_t* src, uint64_t* dst, int64_t n_ct, const int64_t* share, const Geo& G,
-                         const View& V, const Consts& C, const Tables& T, hipStream_t s) {
-  if (n_ct <= 0) return hipSuccess;
-  NTT_DISPATCH(k_ntt_ct, dim3((unsigned)(n_ct * C.L)), C, s, src, dst, n_ct, share, G, V, C, T);
-  return hipGetLastError();
-}
-
-hipError_t launch_ntt_pt(const int64_t* tensor, uint64_t* dst, int64_t n_pt, int side, const Geo& G, const View& V,
-                         const Consts& C, const Tables& T, hipStream_t s) {
-  if (n_pt <= 0) return hipSuccess;
-  NTT_DISPATCH(k_ntt_pt, dim3((unsigned)(n_pt * C.L)), C, s, tensor, dst, n_pt, side, G, V, C, T);
-  return hipGetLastError();
-}
-
 hipError_t launch_ntt_ternary(uint64_t* dst, int64_t count, uint64_t nonce, uint64_t obj_base, uint32_t purpose, int form,
                               const Consts& C, const Tables& T, hipStream_t s) {
   if (count <= 0) return hipSuccess;
@@ -62,8 +34,7 @@ hipError_t configure_lds_ntt() {
   const int max_lds = 160 * 1024;
   hipError_t e = hipSuccess;
 #define PENCIL_RAISE(LN, LE, F)                                                                            \
-  for (const void* f : {(const void*)k_ntt_plain<LN, LE, F>, (const void*)k_ntt_ct<LN, LE, F>,                 \
-                        (const void*)k_ntt_pt<LN, LE, F>, (const void*)k_ntt_ternary<LN, LE, F>}) {            \
+  for (const void* f : {(const void*)k_ntt_plain<LN, LE, F>, (const void*)k_ntt_ternary<LN, LE, F>}) {            \
     hipError_t r = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, max_lds);         \
     if (r != hipSuccess) e = r;                                                                          \
   }

@@ -157,12 +157,34 @@ struct StepSeg {
   MacArgs mac;
 };
 
+// The forward transforms of one product as one launch, passed by value: up to
+// kNttSegs operands, segment i taking the blocks before block_end.
+constexpr int kNttSegs = 4;
+struct NttSeg {
+  int64_t block_end, count;  // count: tiles of the operand
+  int32_t kind, side;        // SEG_CT, SEG_PT, SEG_TERN
+  uint32_t purpose, pad;
+  uint64_t obj_base;
+  const uint64_t* src;
+  uint64_t* dst;
+  const int64_t* tensor;
+  View V;
+};
+struct NttCall {
+  NttSeg seg[kNttSegs];
+  Geo G;
+  Consts C;
+  Tables T;
+  uint64_t nonce;
+};
+
 struct StepPhase {
   const StepSeg* segs;
   int32_t nseg, pad;
   const Consts* consts;      // per context of the step
   const Tables* tabs;
   const uint64_t* nonce;     // base nonce in device memory
+  const NttCall* call;       // forward transforms: one product's (host memory), instead of the tables above
 };
 
 // Output-chunk shape of each MAC variant and the number of chunks it needs.
@@ -197,10 +219,6 @@ __host__ __device__ inline int64_t mac_matrix_groups(int n, int limbs) { return 
 // (defined in kernels.hip; all enqueue on `stream` and return the launch status)
 hipError_t launch_ntt_plain(uint64_t* data, int64_t polys, bool inverse, const Consts& C, const Tables& T,
                             hipStream_t s);
-hipError_t launch_ntt_ct(const uint64_t* src, uint64_t* dst, int64_t n_ct, const int64_t* share, const Geo& G,
-                         const View& V, const Consts& C, const Tables& T, hipStream_t s);
-hipError_t launch_ntt_pt(const int64_t* tensor, uint64_t* dst, int64_t n_pt, int side, const Geo& G, const View& V,
-                         const Consts& C, const Tables& T, hipStream_t s);
 hipError_t launch_ntt_ternary(uint64_t* dst, int64_t count, uint64_t nonce, uint64_t obj_base, uint32_t purpose, int form,
                               const Consts& C, const Tables& T, hipStream_t s);
 hipError_t launch_mac(const MacArgs& A, int64_t n_out, const Geo& G, const Consts& C, hipStream_t s);
