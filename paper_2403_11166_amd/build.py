@@ -14,7 +14,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJDIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libpencil.so")
 SOURCES = [os.path.join(CSRC, f) for f in
-           ("k_ntt.hip", "k_step.hip", "k_do.hip", "k_mac.hip", "k_macx.hip", "k_misc.hip", "host.cpp")]
+           ("k_ntt.hip", "k_step.hip", "k_do.hip", "k_mac.hip", "k_macx.hip", "k_ztx.hip", "k_misc.hip", "host.cpp")]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [

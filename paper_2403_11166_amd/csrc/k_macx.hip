@@ -1,5 +1,5 @@
 // Pointwise multiply-accumulate of the product path on the int8 matrix cores.
-#include "device_common.h"
+#include "mx_common.h"
 
 namespace pencil {
 
@@ -59,10 +59,6 @@ constexpr int kMxBufBytes = 2 * kMxOpBytes;
 constexpr int kMxLds = 2 * kMxBufBytes;
 constexpr int kMxDiag = 15;
 
-typedef int mx_v4i __attribute__((ext_vector_type(4)));
-typedef uint32_t mx_u2 __attribute__((ext_vector_type(2)));
-typedef uint32_t mx_u4 __attribute__((ext_vector_type(4)));
-
 // Split-form residue -> digit bytes (low and high words).
 __device__ __forceinline__ mx_u2 mx_digits(mx_u2 s) {
   const uint64_t v = ((uint64_t)(s[1] >> 2) << 32 | (s[0] | s[1] << 30)) + 0x8080808080808080ull;
@@ -72,15 +68,6 @@ __device__ __forceinline__ mx_u2 mx_digits(mx_u2 s) {
 // The same bytes in reverse order.
 __device__ __forceinline__ mx_u2 mx_reversed(mx_u2 d) {
   return mx_u2{__builtin_bswap32(d[1]), __builtin_bswap32(d[0])};
-}
-
-// Window o of the reversed bytes (r0 = bytes 0..3, r1 = bytes 4..7).
-template <int O>
-__device__ __forceinline__ uint32_t mx_window(uint32_t r0, uint32_t r1) {
-  if constexpr (O < 0) return r0 << (-8 * O);
-  else if constexpr (O == 0) return r0;
-  else if constexpr (O < 4) return __builtin_amdgcn_alignbyte(r1, r0, O);
-  else return r1 >> (8 * (O - 4));
 }
 
 // The two instructions of window O.  Windows are formed one at a time: eleven at
@@ -112,10 +99,6 @@ __device__ __forceinline__ void mx_block(mx_v4i (&acc)[kMxDiag], const uint8_t* 
   mx_step<-3>(acc, xl, xh, r0, r1);
   mx_step<7>(acc, xl, xh, r0, r1);
 }
-
-// acc + d m for a 32-bit signed d, one v_mad_i64_i32 (m is kept opaque so that a
-// power of two does not become a sign extension, a shift and an addition).
-__device__ __forceinline__ int64_t mx_mad(int32_t d, int32_t m, int64_t acc) { return acc + (int64_t)d * m; }
 
 // One output from its 15 diagonals: sum_s D_s 2^(8 s) + pk u' mod q.  The
 // diagonals combine in four positive 64-bit groups g_h = 2^56 + sum_{s < 4}

@@ -439,10 +439,6 @@ __global__ void __launch_bounds__(1024) k_zt_mfma(const int64_t* a, const int64_
 // advances its index by the mixed-radix digits (D.dk, D.ddy, D.ddx) of the
 // stride 64 NWB.  WIN = false is the fully connected form (1 x 1 kernel and
 // output, no padding): the contraction index is the channel alone.
-struct DotStep {
-  int32_t dk, ddy, ddx, pad;
-};
-
 template <int NWB, bool WIN>
 __global__ void __launch_bounds__(256) k_zt_dot(const int64_t* a, const int64_t* kt, int64_t* out, Geo G, View AV,
                                                 View KV, View OV, Consts C, DotStep D) {
@@ -895,6 +891,13 @@ hipError_t launch_stride_relayout(const Relayout& R, const int64_t* in, int64_t*
 
 constexpr int64_t kDotMinK = 256, kDotWideK = 8192, kDotMaxTiles = 64, kMfmaMinTiles = 256, kMfmaMinWaves = 512;
 constexpr int kDotMaxSkinny = 4;
+constexpr int64_t kZxMinWork = (int64_t)1 << 26;
+
+// Distance from a view's first to its last element that k_zt_matrix computes
+// with in 32 bits (window positions outside the tensor are not read).
+static int64_t zx_extent(const View& V, int64_t n0, int64_t n1, int64_t h, int64_t w) {
+  return (n0 - 1) * V.s0 + (n1 - 1) * V.s1 + (h - 1) * V.sy + (w - 1) * V.sx;
+}
 
 hipError_t launch_zt_corr(const int64_t* a, const int64_t* k, int64_t* out, const Geo& G, const View& AV,
                           const View& KV, const View& OV, const Consts& C, hipStream_t s) {
@@ -910,6 +913,19 @@ hipError_t launch_zt_corr(const int64_t* a, const int64_t* k, int64_t* out, cons
   const int mb = std::max(42, std::max(22 + hb, 2 * hb));
   const int64_t per_wave_max = mb >= 63 ? 1 : (int64_t)1 << (64 - mb);
   const int64_t tiles = ((rows + 15) / 16) * ((G.R + 15) / 16);
+  const int kk1 = G.KH * G.KW;
+  const bool win = !(kk1 == 1 && G.OH == 1 && G.OW == 1 && AV.H == 1 && AV.W == 1 && AV.pad == 0 && AV.pady == 0);
+  // int8 matrix kernel (64 x 64 outputs, the contraction split over workgroups):
+  // large correlations of values below 2^46 with at least five columns.  Measured
+  // against the kernels below: from 113 M multiply-adds faster throughout (64 x
+  // 2048 x 1001 FC: 49 -> 25, 54 -> 20, 92 -> 21 us; 3 -> 64 channels on 32 x 32:
+  // 143 -> 36, 129 -> 65; Conv1d 128 -> 128: 83 -> 43, 83 -> 47, 76 -> 35); up to
+  // 15 M the split's clearing and reduction launches cost more than it gains in
+  // most (128 x 256 x 256 FC: 11 -> 13 us).  The line lies between.
+  if (C.t < (1ull << 46) && G.R > kDotMaxSkinny && rows < (1ll << 31) && ctot < (1ll << 28) &&
+      rows * G.R * ctot >= kZxMinWork && ((rows + 63) / 64) * (((int64_t)G.R + 63) / 64) < (1ll << 31) &&
+      zx_extent(AV, G.M, G.K, G.OH + G.KH, G.OW + G.KW) < (1ll << 30) && zx_extent(KV, G.R, G.K, G.KH, G.KW) < (1ll << 30))
+    return launch_zt_matrix(a, k, out, G, AV, KV, OV, C, win, s);
   // Long contractions whose outputs fill few 16 x 16 tiles, or only a few
   // columns of each (at most kDotMaxSkinny, where the other kernels' tiles
   // would compute mostly padding): 2 x 2 output blocks, the lanes of one wave
@@ -921,7 +937,6 @@ hipError_t launch_zt_corr(const int64_t* a, const int64_t* k, int64_t* out, cons
     const int kk = G.KH * G.KW, st = 64 * nwb;
     const DotStep D{st / kk, (st % kk) / G.KW, (st % kk) % G.KW, 0};
     const int64_t grid = nwb == 4 ? blocks : (blocks + 3) / 4;
-    const bool win = !(kk == 1 && G.OH == 1 && G.OW == 1 && AV.H == 1 && AV.W == 1 && AV.pad == 0 && AV.pady == 0);
     if (grid < (1ll << 31)) {
       const dim3 g((unsigned)grid), b(256);
       if (nwb == 4 && win)

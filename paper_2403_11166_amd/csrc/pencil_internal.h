@@ -259,6 +259,28 @@ hipError_t launch_stride_relayout(const Relayout& R, const int64_t* in, int64_t*
 hipError_t launch_zt_corr(const int64_t* a, const int64_t* k, int64_t* out, const Geo& G, const View& AV,
                           const View& KV, const View& OV, const Consts& C, hipStream_t s);
 // width: ntt_loge, plus 8 for contexts with fold60
+// The lane-split and matrix-core Z_t correlations advance a contraction index
+// (k, dy, dx) by the mixed-radix digits of their stride.
+struct DotStep {
+  int32_t dk, ddy, ddx, pad;
+};
+constexpr int64_t kZxMaxK = 8192;  // contraction indices one workgroup's int32 accumulators take
+// Parts the contraction is split into.  A CU holds one workgroup (144 VGPRs), so
+// the grid is at most one per CU, or two when that leaves clearly fewer CUs idle;
+// a part has at least four turns of 16 indices.  Weight gradient of a 64 -> 64
+// channel 3 x 3 layer on 16 x 16, batch 64 (9 tiles): 252 workgroups 67 us, 504
+// 87 us, 513 (a last round of one) 108 us; of a 256 -> 256 one on 8 x 8 (144
+// tiles): 144 workgroups 246 us, 432 201 us.
+inline int64_t zt_matrix_splits(int64_t tiles, int64_t ctot) {
+  int64_t s = 256 / tiles;
+  if (5 * (512 / tiles) > 12 * s) s = 512 / tiles;
+  if (s > ctot / 64) s = ctot / 64;
+  const int64_t least = (ctot + kZxMaxK - 1) / kZxMaxK;
+  if (s < least) s = least;
+  return s < 1 ? 1 : s;
+}
+hipError_t launch_zt_matrix(const int64_t* a, const int64_t* k, int64_t* out, const Geo& G, const View& AV,
+                            const View& KV, const View& OV, const Consts& C, bool win, hipStream_t s);
 hipError_t launch_step_ntt(int log2n, int width, bool inverse, const StepPhase& P, int64_t blocks, hipStream_t s);
 hipError_t launch_step_mac(const StepPhase& P, int64_t blocks, int kind, hipStream_t s);
 hipError_t launch_step_mac_matrix(const StepPhase& P, int64_t blocks, hipStream_t s);
