@@ -60,8 +60,15 @@ __global__ void PENCIL_NTT_BOUNDS(LOGN, LOGE) k_phase(const uint64_t* ct, uint64
   const int64_t j = p / L;
   const LimbConst& lc = C.limb[l];
   const uint64_t* c0 = ct + ((j * 2 + 0) * L + l) * n;
+  // residues as the caller has them, sums of ciphertexts unreduced: any
+  // representative for the F60 butterflies, below 16 q for the others
   const uint64_t* c1 = ct + ((j * 2 + 1) * L + l) * n;
-  for (int i = threadIdx.x; i < n; i += blockDim.x) lds[lpad(i)] = c1[i];
+  if constexpr (F60) {
+    const BflyK<true> bk = bfly_consts<true>(lc.q);
+    for (int i = threadIdx.x; i < n; i += blockDim.x) lds[lpad(i)] = fold60(c1[i], bk);
+  } else {
+    for (int i = threadIdx.x; i < n; i += blockDim.x) lds[lpad(i)] = c1[i];
+  }
   __syncthreads();
   ntt_fwd<LOGN, LOGE, F60>(lds, T.fw + (int64_t)l * n, lc.q);
   const uint64_t* sv = s_ntt + (int64_t)l * n;
