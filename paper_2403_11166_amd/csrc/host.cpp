@@ -387,15 +387,6 @@ static void pass_order(const TW* in, TW* out, int logn, int loge, bool inverse) 
   }
 }
 
-// The context's residues per thread (log2), with the tables in its passes' order.
-static void set_ntt_loge(pencil_ctx* ctx, int loge) {
-  Consts& C = ctx->C;
-  const size_t ln = (size_t)C.L * C.n;
-  C.ntt_loge = loge;
-  ctx->T.fw = ctx->d_tables + 2 * (size_t)(loge - 4) * ln;
-  ctx->T.iw = ctx->T.fw + ln;
-}
-
 extern "C" pencil_status pencil_ctx_create(const pencil_params* params, pencil_ctx** out) {
   if (!out) return fail(nullptr, PENCIL_EINVAL, "out is NULL");
   *out = nullptr;
@@ -448,7 +439,8 @@ extern "C" pencil_status pencil_ctx_create(const pencil_params* params, pencil_c
     return cleanup(fail(nullptr, PENCIL_ENOMEM, "device allocation failed"));
   if (hipMemcpy(ctx->d_tables, tab.data(), tab.size() * sizeof(TW), hipMemcpyHostToDevice) != hipSuccess)
     return cleanup(fail(nullptr, PENCIL_EHIP, "table upload failed"));
-  set_ntt_loge(ctx, C.ntt_loge);
+  ctx->T.fw = ctx->d_tables;
+  ctx->T.iw = ctx->d_tables + L * n;
   // keys
   if (launch_keygen(ctx->d_s_ntt, ctx->d_s_coeff, ctx->d_pk_coeff, ctx->d_pk_ntt, C, ctx->T, nullptr) != hipSuccess ||
       hipDeviceSynchronize() != hipSuccess)
@@ -1621,6 +1613,9 @@ static pencil_status step_bind_tables(pencil_step* st, const pencil_step_io* io,
     if (misaligned(io[i].ct_x1) || misaligned(io[i].ct_dy_dx) || misaligned(io[i].ct_x_dw) ||
         misaligned(io[i].ct_dy_dw) || misaligned(io[i].ct_y) || misaligned(io[i].ct_dx) || misaligned(io[i].ct_dw))
       return step_fail(st, PENCIL_EINVAL, "a ciphertext buffer is not 16-byte aligned");
+  // one width per context for the whole bind, whatever a tuning on another thread does meanwhile
+  std::vector<int> ntt_key;
+  for (auto* c : st->ctxs) ntt_key.push_back(step_ntt_key(c->C));
   // fixed phase order: forward NTTs, MAC, inverse NTTs, flood (per ring degree / flood width)
   for (int kind = 0; kind < 4; ++kind)
     for (auto& e : st->layers) {
@@ -1628,7 +1623,7 @@ static pencil_status step_bind_tables(pencil_step* st, const pencil_step_io* io,
       if (kind == 1) {  // each multiply-accumulate kernel kind launches separately
         for (int k = 0; k <= kMacMatrix; ++k) phase_for(st, 1, k);
       } else {
-        phase_for(st, kind, kind == 3 ? C.flood_words : step_ntt_key(C));
+        phase_for(st, kind, kind == 3 ? C.flood_words : ntt_key[e.ctx]);
       }
     }
   for (size_t i = 0; i < st->layers.size(); ++i) {
@@ -1653,7 +1648,7 @@ static pencil_status step_bind_tables(pencil_step* st, const pencil_step_io* io,
         return step_fail(st, PENCIL_EINVAL, "missing buffer in step io");
       uint64_t* w = (uint64_t*)((uint8_t*)ws + e.ws_off[op]);
       const uint64_t nonce_off = 2 * (uint64_t)i + (op == 0 ? 0 : 1);
-      auto& ntt = phase_for(st, 0, step_ntt_key(C));
+      auto& ntt = phase_for(st, 0, ntt_key[e.ctx]);
       MacArgs A{};
       A.m_rows = G.nM * G.nOY * G.nOX;
       A.variant = e.P.sched[op];
@@ -1739,7 +1734,7 @@ static pencil_status step_bind_tables(pencil_step* st, const pencil_step_io* io,
       StepSeg si = base;
       si.kind = SEG_INTT;
       si.dst = ct_out;
-      add_seg(phase_for(st, 2, step_ntt_key(C)), si, 2 * no * C.L);
+      add_seg(phase_for(st, 2, ntt_key[e.ctx]), si, 2 * no * C.L);
       StepSeg sf = base;
       sf.kind = SEG_FLOOD;
       sf.dst = ct_out;
@@ -2040,14 +2035,14 @@ extern "C" pencil_status pencil_autotune(pencil_ctx* ctx, const pencil_layer* L,
   std::snprintf(key, sizeof key, "%s N=%d L=%d ntt_loge", arch.c_str(), C.n, C.L);
   if (const std::vector<int>* hit = cache_find(cache, key)) {
     if (hit->size() == 1 && (*hit)[0] >= 4 && (*hit)[0] <= 5 && (C.log2n >= 12 || (*hit)[0] == 4))
-      set_ntt_loge(ctx, (*hit)[0]);
+      C.ntt_loge = (*hit)[0];
   } else {
     std::vector<int> cands = C.log2n >= 12 ? std::vector<int>{4, 5} : std::vector<int>{4};
     std::vector<float> times;
     int bestv = C.ntt_loge;
     float best = -1;
     for (int c : cands) {
-      set_ntt_loge(ctx, c);
+      C.ntt_loge = c;
       const float ms = step_ms(P);
       times.push_back(ms);
       if (ms > 0 && (best < 0 || ms < best)) {
@@ -2055,7 +2050,7 @@ extern "C" pencil_status pencil_autotune(pencil_ctx* ctx, const pencil_layer* L,
         bestv = c;
       }
     }
-    set_ntt_loge(ctx, bestv);
+    C.ntt_loge = bestv;
     fresh.push_back(std::string("{\"key\": \"") + key + "\", \"choice\": " + std::to_string(bestv) +
                     ", \"candidates\": [4, 5], \"ms\": [" + times_str(times) + "]}");
   }

@@ -42,7 +42,7 @@ __global__ void PENCIL_NTT_BOUNDS(LOGN, LOGE) k_encrypt(const uint64_t* u_ntt, c
     }
   }
   __syncthreads();
-  ntt_fwd<LOGN, LOGE, F60>(lds, T.fw + (int64_t)l * n, lc.q);
+  ntt_fwd<LOGN, LOGE, F60>(lds, fw_table<LOGN, LOGE>(T, C, l), lc.q);
   uint64_t* o = ct + p * n;
   for (int i = threadIdx.x; i < n; i += blockDim.x)
     o[i] = split30(add_mod(mul_shoup(u[i], pk[i], pks[i], lc.q), lds[lpad(i)], lc.q));
@@ -70,7 +70,7 @@ __global__ void PENCIL_NTT_BOUNDS(LOGN, LOGE) k_phase(const uint64_t* ct, uint64
     for (int i = threadIdx.x; i < n; i += blockDim.x) lds[lpad(i)] = c1[i];
   }
   __syncthreads();
-  ntt_fwd<LOGN, LOGE, F60>(lds, T.fw + (int64_t)l * n, lc.q);
+  ntt_fwd<LOGN, LOGE, F60>(lds, fw_table<LOGN, LOGE>(T, C, l), lc.q);
   const uint64_t* sv = s_ntt + (int64_t)l * n;
   const uint64_t* ss = s_sh + (int64_t)l * n;
   for (int i = threadIdx.x; i < n; i += blockDim.x) lds[lpad(i)] = mul_shoup(lds[lpad(i)], sv[i], ss[i], lc.q);
@@ -79,7 +79,7 @@ __global__ void PENCIL_NTT_BOUNDS(LOGN, LOGE) k_phase(const uint64_t* ct, uint64
   uint64_t* poly = lds;
   ntt_inv_in<LOGN, LOGE, F60>(
       lds, [poly](int i) { return poly[lpad(i)]; },
-      [o, c0, &lc](int i, uint64_t v) { o[i] = add_mod(c0[i], v, lc.q); }, T.iw + (int64_t)l * n, lc.q);
+      [o, c0, &lc](int i, uint64_t v) { o[i] = add_mod(c0[i], v, lc.q); }, iw_table<LOGN, LOGE>(T, C, l), lc.q);
 }
 
 // Exact decryption of the output slots: with y_l = x_l * (q/q_l)^-1 mod q_l and
@@ -180,7 +180,7 @@ __global__ void PENCIL_NTT_BOUNDS(LOGN, LOGE) k_keygen(uint64_t* s_ntt, int64_t*
   const int l = blockIdx.x;
   const LimbConst& lc = C.limb[l];
   const uint64_t nonce = kKeygenNonce;
-  const TW* tw = T.fw + (int64_t)l * n;
+  const TW* tw = fw_table<LOGN, LOGE>(T, C, l);
   for (int blk = threadIdx.x; blk < n / 8; blk += blockDim.x) {
     U64x4 w = philox((uint64_t)blk, 0, P_SK, 0, C.seed, nonce);
 #pragma unroll
@@ -216,7 +216,7 @@ __global__ void PENCIL_NTT_BOUNDS(LOGN, LOGE) k_keygen(uint64_t* s_ntt, int64_t*
     lds[lpad(i)] = reduce128(ph, pl, lc.q, lc.mu_lo, lc.mu_hi);
   }
   __syncthreads();
-  ntt_inv<LOGN, LOGE, F60>(lds, T.iw + (int64_t)l * n, lc.q);
+  ntt_inv<LOGN, LOGE, F60>(lds, iw_table<LOGN, LOGE>(T, C, l), lc.q);
   __syncthreads();
   for (int blk = threadIdx.x; blk < n / 4; blk += blockDim.x) {
     U64x4 w = philox((uint64_t)blk, 0, P_PK_E, 0, C.seed, nonce);

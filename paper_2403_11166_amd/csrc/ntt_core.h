@@ -24,6 +24,16 @@ struct NttShape {
   static constexpr int start(int i) { return ntt_pass_start(LOGN, LOGE, i); }
 };
 
+// Limb l's twiddles in the order of this width's passes.
+template <int LOGN, int LOGE>
+__device__ __forceinline__ const TW* fw_table(const Tables& T, const Consts& C, int l) {
+  return T.fw + (((int64_t)(LOGE - 4) * 2 * C.L + l) << LOGN);
+}
+template <int LOGN, int LOGE>
+__device__ __forceinline__ const TW* iw_table(const Tables& T, const Consts& C, int l) {
+  return T.iw + (((int64_t)(LOGE - 4) * 2 * C.L + l) << LOGN);
+}
+
 // Launch bounds of a kernel that transforms one polynomial per workgroup:
 // N / E threads (1024 only for E = 16 at N = 16384, one workgroup per CU by
 // LDS) and the waves per SIMD the registers must allow (4 with 16 residues per
@@ -412,12 +422,12 @@ __device__ __forceinline__ void do_ntt_plain(uint64_t* lds, uint64_t* data, int 
       if constexpr (F60) return fold60(g1[i], bfly_consts<true>(lc.q));
       else return g1[i];
     };
-    ntt_fwd_in<LOGN, LOGE, F60>(lds, red, T.fw + (int64_t)l * n, lc.q);
+    ntt_fwd_in<LOGN, LOGE, F60>(lds, red, fw_table<LOGN, LOGE>(T, C, l), lc.q);
     for (int i = threadIdx.x; i < n / 2; i += blockDim.x) g[i] = u64x2{lds[lpad(2 * i)], lds[lpad(2 * i) + 1]};
   } else {
     // results go from registers to memory
     PENCIL_GLOBAL uint64_t* o1 = gview(data + p * n);
-    ntt_inv_in<LOGN, LOGE, F60>(lds, src, [o1](int i, uint64_t x) { o1[i] = x; }, T.iw + (int64_t)l * n, lc.q);
+    ntt_inv_in<LOGN, LOGE, F60>(lds, src, [o1](int i, uint64_t x) { o1[i] = x; }, iw_table<LOGN, LOGE>(T, C, l), lc.q);
   }
 }
 
@@ -449,7 +459,7 @@ __device__ __forceinline__ void do_ntt_ct(uint64_t* lds, const uint64_t* src, ui
     }
     return v;
   };
-  ntt_fwd_in<LOGN, LOGE, F60>(lds, enc, T.fw + (int64_t)l * n, lc.q);
+  ntt_fwd_in<LOGN, LOGE, F60>(lds, enc, fw_table<LOGN, LOGE>(T, C, l), lc.q);
   // 16-byte accesses: a polynomial is 16-byte aligned
   const PENCIL_GLOBAL u64x2* g2 = (const PENCIL_GLOBAL u64x2*)gview(src + at);
   if (form_blocked(form)) {
@@ -495,7 +505,7 @@ __device__ __forceinline__ void do_ntt_pt(uint64_t* lds, const int64_t* tensor, 
       const int64_t off = a_slot_at(G, V, to, i);
       return off >= 0 ? lift(off) : (uint64_t)0;
     };
-    ntt_fwd_in<LOGN, LOGE, F60>(lds, enc, T.fw + (int64_t)l * n, lc.q);
+    ntt_fwd_in<LOGN, LOGE, F60>(lds, enc, fw_table<LOGN, LOGE>(T, C, l), lc.q);
   } else {
     // K tiles hold rt kt kh kw entries, often far fewer than N (a kernel
     // window per channel pair): zero the polynomial, then scatter the entries
@@ -508,7 +518,7 @@ __device__ __forceinline__ void do_ntt_pt(uint64_t* lds, const int64_t* tensor, 
       if (off >= 0 && slot >= 0 && slot < n) lds[lpad(slot)] = lift(off);
     }
     __syncthreads();
-    ntt_fwd<LOGN, LOGE, F60>(lds, T.fw + (int64_t)l * n, lc.q);
+    ntt_fwd<LOGN, LOGE, F60>(lds, fw_table<LOGN, LOGE>(T, C, l), lc.q);
   }
   store_form<LOGN>(dst, V.form, count, L, l, j, [&](int i) { return form_value(lds[lpad(i)], V.form); });
 }
@@ -535,7 +545,7 @@ __device__ __forceinline__ void do_ntt_ternary(uint64_t* lds, uint64_t* dst, uin
     }
   }
   __syncthreads();
-  ntt_fwd<LOGN, LOGE, F60>(lds, T.fw + (int64_t)l * n, lc.q);
+  ntt_fwd<LOGN, LOGE, F60>(lds, fw_table<LOGN, LOGE>(T, C, l), lc.q);
   store_form<LOGN>(dst, form, count, L, l, j, [&](int i) { return form_value(lds[lpad(i)], form); });
 }
 

@@ -61,8 +61,11 @@ __host__ __device__ constexpr int ntt_pass_start(int logn, int loge, int i) {
 }
 
 // NTT tables, each [L][N]: psi^rev(k) (forward) and psi^-rev(k) (inverse), in the
-// order in which the passes of the context's ntt_loge read them (twiddle_at);
-// entries 0 and 1 of the inverse table hold N^-1 and N^-1 psi^-rev(1).
+// order in which the passes of one width (2^loge residues per thread) read them
+// (twiddle_at); entries 0 and 1 of the inverse table hold N^-1 and N^-1
+// psi^-rev(1).  fw and iw are those of loge = 4; loge = 5 has its own pair 2 L N
+// entries later.  A kernel takes the pair of the width it is compiled for
+// (fw_table, iw_table), so nothing depends on when a width was chosen.
 struct Tables {
   const TW* fw;
   const TW* iw;
