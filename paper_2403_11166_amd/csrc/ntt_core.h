@@ -211,8 +211,11 @@ __device__ __forceinline__ uint64_t reduce_16q(uint64_t x, uint64_t q, const Bfl
 // read consecutive entries.  (In the tables' natural order a thread's entries
 // are adjacent instead: each 16-byte load then touched 64 cache lines and the
 // L1, which 16 waves overran, fetched every line several times: 1.15 MB per
-// polynomial of 128 KB.)  Blocks of 64 or more groups are the same for a whole
-// wave, which reads its twiddles through the scalar cache.
+// polynomial of 128 KB.)  With blocks of 64 or more groups a whole wave uses the
+// same entries.  The F60 passes read these through the scalar cache.  The others
+// measured faster with vector loads, scalar against vector: encryption at N = 4096,
+// L = 2, 50-bit moduli, of 30 ciphertexts 22.7 and 21.8 us, of 1024 189 and 186 us;
+// transforms of a step and the inverse the same.
 template <int B0, bool UNIFORM>
 __device__ __forceinline__ TW twiddle_at(const PENCIL_GLOBAL TW* tw, int e, int blk) {
   if constexpr (UNIFORM) {
@@ -263,7 +266,7 @@ __device__ __forceinline__ void fwd_pass(uint64_t* a, In in, const PENCIL_GLOBAL
       const int blk = (r * T + tid) >> LT;
 #pragma unroll
       for (int j = 0; j < (1 << s); ++j) {
-        const TW w = twiddle_at<S0, (LT >= 6)>(tw, (1 << s) + j, blk);
+        const TW w = twiddle_at<S0, (F60 && LT >= 6)>(tw, (1 << s) + j, blk);
 #pragma unroll
         for (int k = j << (S - s); k < ((j + 1) << (S - s)); ++k) {
           if (k & h) continue;
@@ -314,12 +317,12 @@ __device__ __forceinline__ void inv_pass(In in, Out out, const PENCIL_GLOBAL TW*
       const int blk = (r * T + tid) >> L0;
 #pragma unroll
       for (int j = 0; j < (K >> (s + 1)); ++j) {
-        const TW w = twiddle_at<LOGN - L0 - S, (L0 >= 6)>(tw, (K >> (s + 1)) + j, blk);
+        const TW w = twiddle_at<LOGN - L0 - S, (F60 && L0 >= 6)>(tw, (K >> (s + 1)) + j, blk);
 #pragma unroll
         for (int k = j << (s + 1); k < ((j + 1) << (s + 1)); ++k) {
           if (k & h) continue;
           if (LAST && s == S - 1)
-            gs_last(v[r * K + k], v[r * K + k + h], twiddle_at<0, true>(tw, 0, 0), w, bk, L0 + s);
+            gs_last(v[r * K + k], v[r * K + k + h], twiddle_at<0, F60>(tw, 0, 0), w, bk, L0 + s);
           else
             gs_bfly(v[r * K + k], v[r * K + k + h], w, bk, L0 + s);
         }
