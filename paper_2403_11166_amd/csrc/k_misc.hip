@@ -899,6 +899,21 @@ static int64_t zx_extent(const View& V, int64_t n0, int64_t n1, int64_t h, int64
   return (n0 - 1) * V.s0 + (n1 - 1) * V.s1 + (h - 1) * V.sy + (w - 1) * V.sx;
 }
 
+// Few columns fill a quarter of a 64 x 64 tile or less, and a grid of a little more
+// than one workgroup per CU then runs a second round for little: the f64 matrix
+// kernel, whose tiles are 16 columns wide, can be faster.  Both sides' times in ns,
+// fitted to windowed correlations of 5 to 14 columns, 258 to 819 tiles and 375 to
+// 4225 indices (within 8 %): 169 -> 6 channels, 5 x 5 valid window on 29 x 29 images, batch
+// 30 (293 tiles): 498 us there, 420 in the f64 kernel; 12 columns, 756
+// indices, 258 tiles: 97 and 106.  From 2^42 the f64 kernel takes three digits, and
+// past 2^15 indices its waves' sums do not hold two.
+static bool zx_slower(int64_t rows, int r, int64_t ctot, bool contiguous_cols, bool win, uint64_t t) {
+  if (!win || r > 16 || t >= (1ull << 42) || ctot > (1 << 15)) return false;
+  const int64_t grid = (rows + 63) / 64, rounds = (grid + 255) / 256;
+  if (rounds < 2 || zt_matrix_splits(grid, ctot, contiguous_cols) > 1) return false;
+  return (rows + 15) / 16 * (48000 + 74 * ctot) / 1000 < rounds * (8000 + 59 * ctot);
+}
+
 hipError_t launch_zt_corr(const int64_t* a, const int64_t* k, int64_t* out, const Geo& G, const View& AV,
                           const View& KV, const View& OV, const Consts& C, hipStream_t s) {
   const int64_t total = (int64_t)G.M * G.R * G.OH * G.OW;
@@ -917,14 +932,17 @@ hipError_t launch_zt_corr(const int64_t* a, const int64_t* k, int64_t* out, cons
   const bool win = !(kk1 == 1 && G.OH == 1 && G.OW == 1 && AV.H == 1 && AV.W == 1 && AV.pad == 0 && AV.pady == 0);
   // int8 matrix kernel (64 x 64 outputs, the contraction split over workgroups):
   // large correlations of values below 2^46 with at least five columns.  Measured
-  // against the kernels below: from 113 M multiply-adds faster throughout (64 x
-  // 2048 x 1001 FC: 49 -> 25, 54 -> 20, 92 -> 21 us; 3 -> 64 channels on 32 x 32:
-  // 143 -> 36, 129 -> 65; Conv1d 128 -> 128: 83 -> 43, 83 -> 47, 76 -> 35); up to
-  // 15 M the split's clearing and reduction launches cost more than it gains in
-  // most (128 x 256 x 256 FC: 11 -> 13 us).  The line lies between.
+  // on 550 shapes of FC, Conv1d and Conv2d operators from 67 M to 600 M multiply-adds
+  // against the kernels below: 2.6 times as fast in the mean, 0.98 at the lowest but
+  // for what zx_slower leaves them (64 x 2048 x 1001 FC: 49 -> 25, 54 -> 20, 92 -> 21
+  // us; 3 -> 64 channels on 32 x 32: 143 -> 36, 129 -> 65; Conv1d 128 -> 128: 83 -> 43,
+  // 83 -> 47, 76 -> 35).  Under the line the clearing and reduction launches count: at
+  // 6 M mostly slower (980 x 100 FC, batch 64: 10.5 -> 13.7 us), at 17 to 38 M from
+  // 0.7 to 3 times as fast.
   if (C.t < (1ull << 46) && G.R > kDotMaxSkinny && rows < (1ll << 31) && ctot < (1ll << 28) &&
       rows * G.R * ctot >= kZxMinWork && ((rows + 63) / 64) * (((int64_t)G.R + 63) / 64) < (1ll << 31) &&
-      zx_extent(AV, G.M, G.K, G.OH + G.KH, G.OW + G.KW) < (1ll << 30) && zx_extent(KV, G.R, G.K, G.KH, G.KW) < (1ll << 30))
+      zx_extent(AV, G.M, G.K, G.OH + G.KH, G.OW + G.KW) < (1ll << 30) &&
+      zx_extent(KV, G.R, G.K, G.KH, G.KW) < (1ll << 30) && !zx_slower(rows, G.R, ctot, OV.s1 == 1, win, C.t))
     return launch_zt_matrix(a, k, out, G, AV, KV, OV, C, win, s);
   // Long contractions whose outputs fill few 16 x 16 tiles, or only a few
   // columns of each (at most kDotMaxSkinny, where the other kernels' tiles
@@ -957,7 +975,9 @@ hipError_t launch_zt_corr(const int64_t* a, const int64_t* k, int64_t* out, cons
   // below 2^(bitlen(t) - 22)) 2^42; with three 14-bit digits 2^30 (t < 2^43;
   // 2^(2 bitlen(t) - 58) above).  Taken when its grid has at least
   // kMfmaMinTiles tiles or kMfmaMinWaves waves; smaller grids measured faster
-  // on the vector kernel, whose 8 x 8 tiles spread the work over more waves.
+  // on the vector kernel, whose 8 x 8 tiles spread the work over more waves.  For
+  // t < 2^42 more steps than two digits hold only come with operands that the
+  // int8 kernel's 32-bit offsets do not reach.
   {
     const int64_t steps = (ctot + 3) / 4;
     const int nwm = (int)std::min<int64_t>(kZtWaves, std::max<int64_t>(1, steps / 8));

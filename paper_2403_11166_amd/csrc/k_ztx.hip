@@ -215,7 +215,7 @@ hipError_t launch_zt_matrix(const int64_t* a, const int64_t* k, int64_t* out, co
                             const View& KV, const View& OV, const Consts& C, bool win, hipStream_t s) {
   const int64_t rows = (int64_t)G.M * G.OH * G.OW, ctot = (int64_t)G.K * G.KH * G.KW, count = rows * G.R;
   const int64_t rbs = (rows + kZxTile - 1) / kZxTile, cbs = ((int64_t)G.R + kZxTile - 1) / kZxTile;
-  const int64_t splits = zt_matrix_splits(rbs * cbs, ctot);
+  const int64_t splits = zt_matrix_splits(rbs * cbs, ctot, OV.s1 == 1);
   const int64_t turns = (ctot + kZxKB - 1) / kZxKB, per = (turns + splits - 1) / splits * kZxKB;
   const int kk = G.KH * G.KW;
   const DotStep D{kZxKB / kk, (kZxKB % kk) / G.KW, (kZxKB % kk) % G.KW, 0};

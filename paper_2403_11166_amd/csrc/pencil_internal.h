@@ -269,15 +269,22 @@ struct DotStep {
 };
 constexpr int64_t kZxMaxK = 8192;  // contraction indices one workgroup's int32 accumulators take
 // Parts the contraction is split into.  A CU holds one workgroup (144 VGPRs), so
-// the grid is at most one per CU, or two when that leaves clearly fewer CUs idle;
-// a part has at least four turns of 16 indices.  Weight gradient of a 64 -> 64
-// channel 3 x 3 layer on 16 x 16, batch 64 (9 tiles): 252 workgroups 67 us, 504
-// 87 us, 513 (a last round of one) 108 us; of a 256 -> 256 one on 8 x 8 (144
-// tiles): 144 workgroups 246 us, 432 201 us.
-inline int64_t zt_matrix_splits(int64_t tiles, int64_t ctot) {
+// the grid is at most one per CU, or two when that leaves clearly fewer CUs idle
+// and the parts are long enough (a grid cut to between one and two runs a nearly
+// empty round).  Weight gradient of a 64 -> 64 channel 3 x 3 layer on 16 x 16,
+// batch 64 (9 tiles): 252 workgroups 67 us, 504 87 us, 513 (a last round of one)
+// 108 us; of a 256 -> 256 one on 8 x 8 (144 tiles): 144 workgroups 246 us, 432 201
+// us.  A part has at least 64 indices where a tile's columns are contiguous in the
+// output (a wave's 16 atomic additions fall on one line), and 168 where each falls
+// on a line of its own and the additions cost as much as the products: input
+// gradient of a Conv1d 128 -> 256, k = 5, length 30, batch 16 (16 tiles, 983 k
+// additions in 16 parts) 46 us, in 7 parts 30 us, and 32 us in the f64 kernel; weight
+// gradient of an FC 784 -> 800, batch 128, in two parts 43 us, in one 15 us, and 40 us there.
+inline int64_t zt_matrix_splits(int64_t tiles, int64_t ctot, bool contiguous_cols) {
+  const int64_t most = ctot / (contiguous_cols ? 64 : 168), two = 512 / tiles;
   int64_t s = 256 / tiles;
-  if (5 * (512 / tiles) > 12 * s) s = 512 / tiles;
-  if (s > ctot / 64) s = ctot / 64;
+  if (5 * two > 12 * s && two <= most) s = two;
+  if (s > most) s = most;
   const int64_t least = (ctot + kZxMaxK - 1) / kZxMaxK;
   if (s < least) s = least;
   return s < 1 ? 1 : s;
