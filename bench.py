@@ -216,20 +216,20 @@ def kernel_work(sizes_list):
                 n_ct_in, n_pt = sz.n_ct[2] + sz.n_ct[3], sz.n_pt[2]
             add = lambda k, b, o: work.__setitem__(k, (work.get(k, (0, 0))[0] + b, work.get(k, (0, 0))[1] + o))  # noqa
             b10 = MUL32_PER_BUTTERFLY * bfly
-            # input ciphertexts arrive in the NTT domain (split form) and are read
-            # in place by the multiply-accumulate; forward and input-gradient
-            # ciphertexts get the model owner's share transformed and added to
-            # component 0, which is read and written once (staged copy)
-            add("ntt_ct", (2 * n_ct_in * poly if op != "dw" else 0), (n_ct_in if op != "dw" else 0) * b10)
-            add("ntt_pt", n_pt * poly, n_pt * b10)
-            add("ntt_ternary", n_out * poly, n_out * b10)
+            # one launch holds a product's forward transforms: plaintexts, masks and,
+            # for the forward and input-gradient products, the model owner's share,
+            # added to component 0 of the input ciphertexts, which is read and
+            # written once (staged copy; they arrive in the NTT domain, and the
+            # multiply-accumulate reads the rest in place)
+            n_share = n_ct_in if op != "dw" else 0
+            add("ntt_ct" if n_share else "ntt_pt", (2 * n_share + n_pt + n_out) * poly, (n_share + n_pt + n_out) * b10)
             add("mac", (2 * n_ct_in + n_pt + n_out + 2 * n_out) * poly,
                 MUL32_PER_MAC * sz.n_products[opi] * 2 * L * n)
             add("intt_out", 2 * n_out * 2 * poly, 2 * n_out * b10)
             add("flood_mask", 2 * n_out * 2 * poly, 0)
     # the batched step's phase launches cover the same work
     get = lambda k: work.get(k, (0, 0))  # noqa: E731
-    work["step_ntt"] = tuple(get("ntt_ct")[i] + get("ntt_pt")[i] + get("ntt_ternary")[i] for i in range(2))
+    work["step_ntt"] = tuple(get("ntt_ct")[i] + get("ntt_pt")[i] for i in range(2))
     work["step_mac"] = get("mac")
     work["step_intt"] = get("intt_out")
     work["step_flood"] = get("flood_mask")

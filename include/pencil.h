@@ -439,7 +439,10 @@ pencil_status pencil_probe_mul32(int kind, double* per_s /* host */);
 /* Kernel timing: while enabled, every kernel this context launches is bracketed
  * by HIP events recorded on its launch stream.  enable() clears the totals.
  * read() waits for the recorded events and fills up to `max` entries (host
- * memory): kernel name, launches and summed milliseconds. */
+ * memory): kernel name, launches and summed milliseconds.  The forward transforms
+ * of one product outside a step are one launch: ntt_ct where it adds the share to
+ * the input ciphertexts (forward and input gradient), ntt_pt for the weight
+ * gradient; ntt_ternary is the encryption's. */
 typedef struct {
     char name[24];
     uint64_t launches;

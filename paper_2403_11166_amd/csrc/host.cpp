@@ -49,10 +49,10 @@ struct pencil_ctx {
 };
 
 enum KernelId {
-  KID_NTT_TERNARY, KID_MAC, KID_INTT_OUT, KID_FLOOD, KID_ENCRYPT, KID_PHASE, KID_DECODE,
+  KID_NTT_CT, KID_NTT_PT, KID_NTT_TERNARY, KID_MAC, KID_INTT_OUT, KID_FLOOD, KID_ENCRYPT, KID_PHASE, KID_DECODE,
   KID_NTT_PLAIN, KID_STEP_NTT, KID_STEP_MAC, KID_STEP_INTT, KID_STEP_FLOOD, KID_COUNT
 };
-static const char* kKernelNames[KID_COUNT] = {"ntt_ternary", "mac", "intt_out",
+static const char* kKernelNames[KID_COUNT] = {"ntt_ct", "ntt_pt", "ntt_ternary", "mac", "intt_out",
                                               "flood_mask", "encrypt", "phase", "decode", "ntt_plain",
                                               "step_ntt", "step_mac", "step_intt", "step_flood"};
 
@@ -1051,7 +1051,7 @@ static pencil_status run_product(pencil_ctx* ctx, const pencil_layer* L, int op,
   StepPhase P{};
   P.call = &N;
   if (blocks >= (1ll << 31)) return fail(ctx, PENCIL_EUNSUPPORTED, "too many input tiles for one launch");
-  hipError_t e = timed(ctx, KID_STEP_NTT, s, [&] {
+  hipError_t e = timed(ctx, add_share ? KID_NTT_CT : KID_NTT_PT, s, [&] {
     return launch_step_ntt(C.log2n, step_ntt_key(C) % 16, false, P, blocks, s);
   });
   if (e == hipSuccess) e = timed(ctx, KID_MAC, s, [&] { return launch_mac(A, no, G, C, s); });
