@@ -429,6 +429,11 @@ typedef struct {
 pencil_status pencil_noise_bound(const pencil_params* params, const pencil_layer* layer, const pencil_plan* plan,
                                  int op, uint32_t plaintext_bits, pencil_noise* out /* host */);
 
+/* The kernel of a product's multiply-accumulate under `plan` (host only, no GPU
+ * needed): *matrix is 1 on the matrix cores, 0 on the vector units. */
+pencil_status pencil_product_kernel(const pencil_params* params, const pencil_layer* layer, const pencil_plan* plan,
+                                    int op, int* matrix /* host */);
+
 /* Measurement aid for the integer roofline: the rate, per second over the
  * whole current GPU, of one 32-bit multiply instruction form -- kind 0
  * v_mad_u64_u32 (the multiply-accumulate's), 1 v_mul_lo_u32, 2 v_mul_hi_u32
@@ -442,7 +447,9 @@ pencil_status pencil_probe_mul32(int kind, double* per_s /* host */);
  * memory): kernel name, launches and summed milliseconds.  The forward transforms
  * of one product outside a step are one launch: ntt_ct where it adds the share to
  * the input ciphertexts (forward and input gradient), ntt_pt for the weight
- * gradient; ntt_ternary is the encryption's. */
+ * gradient; ntt_ternary is the encryption's.  mac and step_mac are the
+ * multiply-accumulates on the vector units, mac_matrix and step_mac_matrix those
+ * on the matrix cores. */
 typedef struct {
     char name[24];
     uint64_t launches;

@@ -94,6 +94,8 @@ SIGNATURES = {
     "pencil_probe_mul32": (ctypes.c_int, [ctypes.c_int, ctypes.POINTER(ctypes.c_double)]),
     "pencil_noise_bound": (ctypes.c_int, [ctypes.POINTER(Params), ctypes.POINTER(Layer), ctypes.POINTER(Plan),
                                           ctypes.c_int, ctypes.c_uint32, ctypes.POINTER(Noise)]),
+    "pencil_product_kernel": (ctypes.c_int, [ctypes.POINTER(Params), ctypes.POINTER(Layer), ctypes.POINTER(Plan),
+                                             ctypes.c_int, ctypes.POINTER(ctypes.c_int)]),
     "pencil_profile_enable": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_int]),
     "pencil_profile_read": (ctypes.c_int, [ctypes.c_void_p, ctypes.POINTER(KernelStat), ctypes.c_int,
                                            ctypes.POINTER(ctypes.c_int)]),

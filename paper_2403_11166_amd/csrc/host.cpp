@@ -50,11 +50,13 @@ struct pencil_ctx {
 
 enum KernelId {
   KID_NTT_CT, KID_NTT_PT, KID_NTT_TERNARY, KID_MAC, KID_INTT_OUT, KID_FLOOD, KID_ENCRYPT, KID_PHASE, KID_DECODE,
-  KID_NTT_PLAIN, KID_STEP_NTT, KID_STEP_MAC, KID_STEP_INTT, KID_STEP_FLOOD, KID_COUNT
+  KID_NTT_PLAIN, KID_STEP_NTT, KID_STEP_MAC, KID_STEP_INTT, KID_STEP_FLOOD,
+  KID_MAC_MATRIX, KID_STEP_MAC_MATRIX, KID_COUNT
 };
 static const char* kKernelNames[KID_COUNT] = {"ntt_ct", "ntt_pt", "ntt_ternary", "mac", "intt_out",
                                               "flood_mask", "encrypt", "phase", "decode", "ntt_plain",
-                                              "step_ntt", "step_mac", "step_intt", "step_flood"};
+                                              "step_ntt", "step_mac", "step_intt", "step_flood",
+                                              "mac_matrix", "step_mac_matrix"};
 
 static hipEvent_t pool_event(pencil_ctx* ctx) {
   if (!ctx->ev_pool.empty()) {
@@ -1054,7 +1056,7 @@ static pencil_status run_product(pencil_ctx* ctx, const pencil_layer* L, int op,
   hipError_t e = timed(ctx, add_share ? KID_NTT_CT : KID_NTT_PT, s, [&] {
     return launch_step_ntt(C.log2n, step_ntt_key(C) % 16, false, P, blocks, s);
   });
-  if (e == hipSuccess) e = timed(ctx, KID_MAC, s, [&] { return launch_mac(A, no, G, C, s); });
+  if (e == hipSuccess) e = timed(ctx, matrix ? KID_MAC_MATRIX : KID_MAC, s, [&] { return launch_mac(A, no, G, C, s); });
   if (e == hipSuccess) e = timed(ctx, KID_INTT_OUT, s, [&] { return launch_ntt_plain(ct_out, 2 * no, true, C, ctx->T, s); });
   if (e == hipSuccess)
     e = timed(ctx, KID_FLOOD, s, [&] {
@@ -1773,7 +1775,7 @@ static hipError_t step_phases(pencil_step* st, hipStream_t s) {
       e = timed(pc, ph.kind == 0 ? KID_STEP_NTT : KID_STEP_INTT, s,
                 [&] { return launch_step_ntt(ph.key / 16, ph.key % 16, ph.kind == 2, P, ph.blocks, s); });
     else if (ph.kind == 1)
-      e = timed(pc, KID_STEP_MAC, s, [&] {  return launch_step_mac(P, ph.blocks, ph.key, s); });
+      e = timed(pc, ph.key == kMacMatrix ? KID_STEP_MAC_MATRIX : KID_STEP_MAC, s, [&] { return launch_step_mac(P, ph.blocks, ph.key, s); });
     else
       e = timed(pc, KID_STEP_FLOOD, s, [&] { return launch_step_flood(ph.key, P, ph.blocks, s); });
     if (e != hipSuccess) return e;
@@ -2169,6 +2171,22 @@ extern "C" pencil_status pencil_noise_bound(const pencil_params* params, const p
     return fail(nullptr, PENCIL_ENOISE,
                 "op %d: worst-case noise 2^%.1f (product 2^%.1f + flood 2^%.1f) reaches Delta/2 = 2^%.1f", op,
                 std::log2(product + flood), out->product_bits, out->flood_bits, out->budget_bits);
+  return PENCIL_OK;
+}
+
+extern "C" pencil_status pencil_product_kernel(const pencil_params* params, const pencil_layer* L, const pencil_plan* P,
+                                               int op, int* matrix) {
+  if (!matrix || op < 0 || op > 2) return fail(nullptr, PENCIL_EINVAL, "bad kernel request");
+  pencil_ctx tmp;  // host-only: parameters and geometry, no device state
+  pencil_status st = resolve_params(params, &tmp);
+  if (st != PENCIL_OK) return st;
+  Geo G;
+  st = get_geo(&tmp, L, P, op, &G);
+  if (st != PENCIL_OK) {
+    g_create_err = tmp.err;
+    return st;
+  }
+  *matrix = mac_use_matrix(tmp.C, op == PENCIL_OP_DW ? 2 : 1, G.nM * G.nOY * G.nOX, G) ? 1 : 0;
   return PENCIL_OK;
 }
 
