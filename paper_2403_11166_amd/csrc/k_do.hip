@@ -42,7 +42,7 @@ __global__ void PENCIL_NTT_BOUNDS(LOGN, LOGE) k_encrypt(const uint64_t* u_ntt, c
     }
   }
   __syncthreads();
-  ntt_fwd<LOGN, LOGE, F60>(lds, fw_table<LOGN, LOGE>(T, C, l), lc.q);
+  ntt_fwd<LOGN, LOGE, F60, F60>(lds, fw_table<LOGN, LOGE>(T, C, l), lc.q);
   uint64_t* o = ct + p * n;
   for (int i = threadIdx.x; i < n; i += blockDim.x)
     o[i] = split30(add_mod(mul_shoup(u[i], pk[i], pks[i], lc.q), lds[lpad(i)], lc.q));

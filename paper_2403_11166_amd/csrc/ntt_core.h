@@ -212,10 +212,10 @@ __device__ __forceinline__ uint64_t reduce_16q(uint64_t x, uint64_t q, const Bfl
 // are adjacent instead: each 16-byte load then touched 64 cache lines and the
 // L1, which 16 waves overran, fetched every line several times: 1.15 MB per
 // polynomial of 128 KB.)  With blocks of 64 or more groups a whole wave uses the
-// same entries.  The F60 passes read these through the scalar cache.  The others
-// measured faster with vector loads, scalar against vector: encryption at N = 4096,
-// L = 2, 50-bit moduli, of 30 ciphertexts 22.7 and 21.8 us, of 1024 189 and 186 us;
-// transforms of a step and the inverse the same.
+// same entries, which SCALAR passes read through the scalar cache.  All do but the
+// encryption's with plain moduli (k_encrypt), N = 4096, L = 2, 50-bit moduli, scalar
+// against vector loads: 30 ciphertexts 22.7 and 21.8 us, 1024 189 and 186 us, but the
+// forward transforms of a step 103.7 and 104.3 us, its inverse 35.4 and 35.7 us.
 template <int B0, bool UNIFORM>
 __device__ __forceinline__ TW twiddle_at(const PENCIL_GLOBAL TW* tw, int e, int blk) {
   if constexpr (UNIFORM) {
@@ -233,7 +233,7 @@ __device__ __forceinline__ TW twiddle_at(const PENCIL_GLOBAL TW* tw, int e, int 
 // takes E / 2^S groups of 2^S residues {base + k * 2^LT}, LT = log2 N - S0 - S.
 // `in(i)` supplies input residue i: the LDS polynomial, or for the first pass
 // values the caller computes (an encoding), which then skip the LDS.
-template <int LOGN, int LOGE, bool F60, int S0, int S, bool LAST, typename In>
+template <int LOGN, int LOGE, bool F60, int S0, int S, bool LAST, bool SCALAR, typename In>
 __device__ __forceinline__ void fwd_pass(uint64_t* a, In in, const PENCIL_GLOBAL TW* tw, uint64_t q,
                                          const BflyK<F60>& bk) {
   using Sh = NttShape<LOGN, LOGE>;
@@ -266,7 +266,7 @@ __device__ __forceinline__ void fwd_pass(uint64_t* a, In in, const PENCIL_GLOBAL
       const int blk = (r * T + tid) >> LT;
 #pragma unroll
       for (int j = 0; j < (1 << s); ++j) {
-        const TW w = twiddle_at<S0, (F60 && LT >= 6)>(tw, (1 << s) + j, blk);
+        const TW w = twiddle_at<S0, (SCALAR && LT >= 6)>(tw, (1 << s) + j, blk);
 #pragma unroll
         for (int k = j << (S - s); k < ((j + 1) << (S - s)); ++k) {
           if (k & h) continue;
@@ -317,12 +317,12 @@ __device__ __forceinline__ void inv_pass(In in, Out out, const PENCIL_GLOBAL TW*
       const int blk = (r * T + tid) >> L0;
 #pragma unroll
       for (int j = 0; j < (K >> (s + 1)); ++j) {
-        const TW w = twiddle_at<LOGN - L0 - S, (F60 && L0 >= 6)>(tw, (K >> (s + 1)) + j, blk);
+        const TW w = twiddle_at<LOGN - L0 - S, (L0 >= 6)>(tw, (K >> (s + 1)) + j, blk);
 #pragma unroll
         for (int k = j << (s + 1); k < ((j + 1) << (s + 1)); ++k) {
           if (k & h) continue;
           if (LAST && s == S - 1)
-            gs_last(v[r * K + k], v[r * K + k + h], twiddle_at<0, F60>(tw, 0, 0), w, bk, L0 + s);
+            gs_last(v[r * K + k], v[r * K + k + h], twiddle_at<0, true>(tw, 0, 0), w, bk, L0 + s);
           else
             gs_bfly(v[r * K + k], v[r * K + k + h], w, bk, L0 + s);
         }
@@ -342,33 +342,33 @@ __device__ __forceinline__ void inv_pass(In in, Out out, const PENCIL_GLOBAL TW*
 // inputs in [0, q) that `in(i)` supplies to the first pass; the transform's
 // first LDS access is the first pass' store, so `a` must not be in use.
 // Callers synchronise after (outputs read).
-template <int LOGN, int LOGE, bool F60, typename In>
+template <int LOGN, int LOGE, bool F60, bool SCALAR = true, typename In>
 __device__ __forceinline__ void ntt_fwd_in(uint64_t* a, In in, const TW* tw_generic, uint64_t q) {
   using Sh = NttShape<LOGN, LOGE>;
   const BflyK<F60> bk = bfly_consts<F60>(q);
   const PENCIL_GLOBAL TW* tw = gview(tw_generic);
   auto lds = [a](int i) { return a[lpad(i)]; };
-  fwd_pass<LOGN, LOGE, F60, Sh::start(0), Sh::size(0), Sh::NP == 1>(a, in, tw, q, bk);
+  fwd_pass<LOGN, LOGE, F60, Sh::start(0), Sh::size(0), Sh::NP == 1, SCALAR>(a, in, tw, q, bk);
   __syncthreads();
   if constexpr (Sh::NP > 1) {
-    fwd_pass<LOGN, LOGE, F60, Sh::start(1), Sh::size(1), Sh::NP == 2>(a, lds, tw, q, bk);
+    fwd_pass<LOGN, LOGE, F60, Sh::start(1), Sh::size(1), Sh::NP == 2, SCALAR>(a, lds, tw, q, bk);
     __syncthreads();
   }
   if constexpr (Sh::NP > 2) {
-    fwd_pass<LOGN, LOGE, F60, Sh::start(2), Sh::size(2), Sh::NP == 3>(a, lds, tw, q, bk);
+    fwd_pass<LOGN, LOGE, F60, Sh::start(2), Sh::size(2), Sh::NP == 3, SCALAR>(a, lds, tw, q, bk);
     __syncthreads();
   }
   if constexpr (Sh::NP > 3) {
-    fwd_pass<LOGN, LOGE, F60, Sh::start(3), Sh::size(3), true>(a, lds, tw, q, bk);
+    fwd_pass<LOGN, LOGE, F60, Sh::start(3), Sh::size(3), true, SCALAR>(a, lds, tw, q, bk);
     __syncthreads();
   }
 }
 
 // Forward transform of the LDS polynomial (inputs in [0, q), outputs in [0, q)).
 // Callers synchronise before (inputs written) and after (outputs read).
-template <int LOGN, int LOGE, bool F60>
+template <int LOGN, int LOGE, bool F60, bool SCALAR = true>
 __device__ __forceinline__ void ntt_fwd(uint64_t* a, const TW* tw_generic, uint64_t q) {
-  ntt_fwd_in<LOGN, LOGE, F60>(a, [a](int i) { return a[lpad(i)]; }, tw_generic, q);
+  ntt_fwd_in<LOGN, LOGE, F60, SCALAR>(a, [a](int i) { return a[lpad(i)]; }, tw_generic, q);
 }
 
 // Inverse transform (inputs in [0, 4q), results in [0, q)) by way of the LDS
