@@ -935,16 +935,21 @@ static int step_ntt_key(const Consts& C) { return C.log2n * 16 + C.ntt_loge + (C
 // Whether a product's multiply-accumulate runs on the matrix cores
 // (k_macx.hip).  First what that kernel's index arithmetic takes: contraction
 // sums within int32, reciprocal divisions of rows, evenly spaced tiles along the
-// contraction, tile numbers below 2^31.  Then the cheaper of two linear models
-// fitted to both kernels' times at N = 8192, L = 3 (13 output grids from 1 x 1 to
-// 33 x 3 tiles, 2 to 128 contraction indices, one and two terms; in ns for 1536
-// slot groups): a 16 x 16 output tile costs 30 us and 13 us per block of 16
-// indices however few of its rows are real, an output of the vector kernel (in
-// 2 x 2 blocks) 0.2 us and 0.0235 us per index.  Near the line both take about
-// the same (8 x 16 outputs, 16 indices: 52 against 62 us; 10 x 32, 13: 176
-// against 159), far from it the ratio reaches 2.2 (16 x 16, 128) and 0.1 (1 x 1).
-// Fewer workgroups than two per CU leave the matrix kernel, with one workgroup
-// per CU and a long prologue, half idle.
+// contraction, tile numbers below 2^31.  Fewer workgroups than two per CU leave
+// the matrix kernel, with one workgroup per CU and a long prologue, half idle.
+// Then the cheaper of two linear costs per slot group: a 16 x 16 output tile costs
+// a fixed part and one per block of 16 indices however few of its rows are real,
+// an output of the vector kernel (in 2 x 2 blocks) a fixed part and one per index.
+// The fixed part of a tile is larger for moduli that are not just below 2^60 (a
+// Barrett reduction of every output).  The line is fitted to both kernels' times,
+// per call and batched, at N = 4096, L = 2 with 50- and 60-bit moduli, N = 8192, L = 3
+// with both and N = 16384, L = 4 (748 products: grids of 8 x 8 to 64 x 64, 24 x 128 and
+// 100 x 10 outputs, 2 to 96 indices, one and two terms), with a matrix kernel that is
+// the slower one weighing six times as much as a vector kernel that is.  On these
+// its choice is 0.2 % above the better one in the mean; at most 8 % where it takes
+// the matrix kernel (40 x 24 outputs, 2 x 12 indices: 1716 against 1851 us), 11 %
+// where it takes the vector kernel (100 x 10, 16, per call: 1605 against 1448 us).
+// Far from it the ratio reaches 2.7 (24 x 128, 96) and 0.2 (8 x 8, 2).
 static bool mac_use_matrix(const Consts& C, int n_terms, int m_rows, const Geo& G) {
   const int64_t ksteps = (int64_t)G.nK * G.nKY * G.nKX, sp = (int64_t)G.nOY * G.nOX;
   if (ksteps * n_terms > kMxMaxK || m_rows >= (1 << 15) || (sp > 1 && G.nKY * G.nKX > 1) || sp >= 256) return false;
@@ -953,7 +958,7 @@ static bool mac_use_matrix(const Consts& C, int n_terms, int m_rows, const Geo& 
   if (total < 512 || total >= (1ll << 31)) return false;
   const int64_t blocks = (ksteps + 15) / 16 * n_terms;
   const int64_t outputs = ((int64_t)m_rows + 1) / 2 * 2 * (((int64_t)G.nR + 1) / 2 * 2);
-  return tiles * (30000 + 13000 * blocks) < outputs * (2000 + 235 * ksteps * n_terms) / 10;
+  return 2 * tiles * ((C.fold60 ? 1690 : 2200) + 325 * blocks) < outputs * (11 + 2 * ksteps * n_terms);
 }
 
 // Element offset from a staged component-0 copy to component 1 of the same
