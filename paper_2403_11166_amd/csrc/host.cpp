@@ -935,7 +935,8 @@ static int step_ntt_key(const Consts& C) { return C.log2n * 16 + C.ntt_loge + (C
 // Whether a product's multiply-accumulate runs on the matrix cores
 // (k_macx.hip).  First what that kernel's index arithmetic takes: contraction
 // sums within int32, reciprocal divisions of rows, evenly spaced tiles along the
-// contraction, tile numbers below 2^31.  Fewer workgroups than two per CU leave
+// contraction, tile numbers below 2^31, and a launch of fewer than 2^32 threads
+// (outputs of 128 GiB at most; the vector kernel has half the threads).  Fewer workgroups than two per CU leave
 // the matrix kernel, with one workgroup per CU and a long prologue, half idle.
 // Then the cheaper of two linear costs per slot group: a 16 x 16 output tile costs
 // a fixed part and one per block of 16 indices however few of its rows are real,
@@ -955,7 +956,7 @@ static bool mac_use_matrix(const Consts& C, int n_terms, int m_rows, const Geo& 
   if (ksteps * n_terms > kMxMaxK || m_rows >= (1 << 15) || (sp > 1 && G.nKY * G.nKX > 1) || sp >= 256) return false;
   if ((n_a_tiles(G) | n_k_tiles(G) | n_out_tiles(G)) >> 31) return false;
   const int64_t tiles = mac_matrix_tiles(n_terms, m_rows, G.nR), total = mac_matrix_groups(C.n, C.L) * tiles;
-  if (total < 512 || total >= (1ll << 31)) return false;
+  if (total < 512 || total > kMxMaxBlocks) return false;
   const int64_t blocks = (ksteps + 15) / 16 * n_terms;
   const int64_t outputs = ((int64_t)m_rows + 1) / 2 * 2 * (((int64_t)G.nR + 1) / 2 * 2);
   return 2 * tiles * ((C.fold60 ? 1690 : 2200) + 325 * blocks) < outputs * (11 + 2 * ksteps * n_terms);
@@ -1662,7 +1663,12 @@ static pencil_status step_bind_tables(pencil_step* st, const pencil_step_io* io,
       if (A.variant < 0 || A.variant >= kMacVariants) return step_fail(st, PENCIL_EINVAL, "schedule variant invalid");
       A.pk = ctx->d_pk_split;
       A.out = ct_out;
-      const bool matrix = mac_use_matrix(C, op == 2 ? 2 : 1, A.m_rows, G);
+      // the step's products on the matrix cores share a launch: one that would take it
+      // past its limit runs on the vector kernel (with the same results)
+      const int64_t mx_blocks =
+          (mac_matrix_groups(C.n, C.L) * mac_matrix_tiles(op == 2 ? 2 : 1, A.m_rows, G.nR) + 7) & ~(int64_t)7;
+      const bool matrix = mac_use_matrix(C, op == 2 ? 2 : 1, A.m_rows, G) &&
+                          phase_for(st, 1, kMacMatrix).blocks + mx_blocks <= kMxMaxBlocks;
       const int form_a = matrix ? FORM_DIGITS : FORM_SPLIT, form_k = matrix ? FORM_REVERSED : FORM_SPLIT;
       A.matrix = matrix;
       StepSeg base{};

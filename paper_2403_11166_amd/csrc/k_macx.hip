@@ -45,7 +45,8 @@ namespace pencil {
 // the waves multiply while the others convert was 3 % slower.
 constexpr int kMxTile = 16, kMxKB = 16;
 constexpr int kMxSlots = 16;  // slots of a workgroup, one per wave
-constexpr int kMxThreads = kMxSlots * 64, kMxPairs = kMxSlots / 2;
+constexpr int kMxPairs = kMxSlots / 2;
+static_assert(kMxThreads == kMxSlots * 64, "one wave per slot");
 // LDS layout of one slot's operand: [4 index groups][low, high digits][16 rows]
 // [4 indices]; a wave's 16-byte reads are contiguous.  The staging threads' writes
 // (8 slot pairs x 4 indices of one row) fall on distinct banks: planes and slots
@@ -386,13 +387,14 @@ hipError_t launch_mac_matrix(const MacArgs& A, const Geo& G, const Consts& C, hi
   const int tiles = mac_matrix_tiles(A.n_terms, A.m_rows, G.nR);
   const int64_t total = mac_matrix_groups(C.n, C.L) * tiles;
   if (total <= 0) return hipSuccess;
-  if (total >= (1ll << 31)) return hipErrorInvalidConfiguration;
+  if (total > kMxMaxBlocks) return hipErrorInvalidConfiguration;
   hipLaunchKernelGGL(k_mac_matrix, dim3((unsigned)total), dim3(kMxThreads), kMxLds, s, A, G, C, tiles, total);
   return hipGetLastError();
 }
 
 hipError_t launch_step_mac_matrix(const StepPhase& P, int64_t blocks, hipStream_t s) {
   if (blocks <= 0) return hipSuccess;
+  if (blocks > kMxMaxBlocks) return hipErrorInvalidConfiguration;
   hipLaunchKernelGGL(k_step_mac_matrix, dim3((unsigned)blocks), dim3(kMxThreads), kMxLds, s, P.segs, P.nseg, P.consts);
   return hipGetLastError();
 }

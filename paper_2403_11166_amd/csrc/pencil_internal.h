@@ -211,6 +211,8 @@ __host__ __device__ inline int mac_chunks(int variant, int m_rows, int n_r) {
 // Matrix-core multiply-accumulate: work per group of 16 NTT slots, in 16 x 16
 // output tiles whose rows are (A row, component) pairs for one term, A rows of
 // one component for two.
+constexpr int kMxThreads = 1024;
+constexpr int64_t kMxMaxBlocks = ((1ll << 32) - 1) / kMxThreads;  // a launch holds below 2^32 threads
 constexpr int kMxMaxK = 8192;  // contraction indices (all terms) its int32 accumulators hold
 __host__ __device__ inline int mac_matrix_tiles(int n_terms, int m_rows, int n_r) {
   const int rt = n_terms == 1 ? (2 * m_rows + 15) / 16 : 2 * ((m_rows + 15) / 16);

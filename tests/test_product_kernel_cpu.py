@@ -49,6 +49,15 @@ def test_matrix_kernel_where_it_is_faster(point):
     assert grid(*point) == 1
 
 
+def test_launch_limit():
+    """A launch holds fewer than 2^32 threads, 1024 per 16 slots and output tile: at N
+    = 16384, L = 4 below 1024 tiles of 16 x 16.  Larger products keep the vector kernel."""
+    assert grid((14, 4, 60), 248, 512, 32, "fwd") == 1  # 31 x 32 tiles
+    assert grid((14, 4, 60), 256, 512, 32, "fwd") == 0  # 32 x 32
+    assert grid((14, 4, 60), 256, 1000, 16, "dw") == 0
+    assert grid((10, 1, 60), 4096, 4096, 16, "dw") == 0
+
+
 def test_requests_are_checked():
     from paper_2403_11166_amd import _abi as A
     layer = fc(4, 5, 6, log2_n=10, num_limbs=2, prime_bits=60)
