@@ -351,7 +351,8 @@ pencil_status pencil_stride_relayout(pencil_ctx* ctx, const pencil_layer* stride
  * each product's partition among the caller's tile and the planner's best-
  * ranked ones (App. A leaves the split of large operands open; the choice is
  * written into the plan's tiles), and each product's multiply-accumulate
- * schedule among all nine (written into plan->sched).  A partition fixes the
+ * schedule among all nine (written into plan->sched; none is measured for a
+ * product on the matrix cores, which run it alike under all).  A partition fixes the
  * ciphertext layout: tune before the DO encrypts with the plan, and give both
  * parties the tuned plan.  Output ciphertexts and shares under one plan are
  * bit-identical for every schedule and NTT width.  cache_path (may be NULL) is

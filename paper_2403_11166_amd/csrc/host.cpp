@@ -2112,6 +2112,10 @@ extern "C" pencil_status pencil_autotune(pencil_ctx* ctx, const pencil_layer* L,
       P->sched[op] = (*hit)[0];
       continue;
     }
+    Geo G;  // the matrix cores run a product whatever its schedule: nothing to measure
+    if (get_geo(ctx, L, P, op, &G) == PENCIL_OK &&
+        mac_use_matrix(C, op == PENCIL_OP_DW ? 2 : 1, G.nM * G.nOY * G.nOX, G))
+      continue;
     std::vector<float> times;
     int bestv = P->sched[op];
     float best = -1;
