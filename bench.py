@@ -34,12 +34,24 @@ HBM_PEAK_GBS = 8000.0
 # v_mul_lo_u32, v_mul_hi_u32) issue at close to that rate: the library's probe
 # (pencil_probe_mul32, `--mul-probe`) measures 30-34 T/s.
 MUL32_PEAK_TOPS = 256 * 64 * 2.4e9 / 1e12
-# 32-bit multiplies the algorithm needs per unit of work with 60-bit residues:
-# a Shoup butterfly (3 for the quotient estimate y1 ws1 + hi(y0 ws1) +
-# hi(y1 ws0), 3 + 3 for the low halves of y w and est q) and a
-# multiply-accumulate of two split 30-bit operands.
-MUL32_PER_BUTTERFLY = 9
+# int8 matrix-core peak: 256 CUs x 8192 operations per clock x 2.4 GHz, dense.
+INT8_PEAK_TOPS = 256 * 8192 * 2.4e9 / 1e12
+# 32-bit multiplies of a butterfly: 5 with moduli within 2^26 below 2^60 (four for
+# the product by the split twiddle, one to fold it), else 9 (3 for Shoup's
+# quotient estimate y1 ws1 + hi(y0 ws1) + hi(y1 ws0), 3 + 3 for the low halves of
+# y w and est q).
+MUL32_PER_BUTTERFLY = {True: 5, False: 9}
+# A multiply-accumulate of two residues: 4 32-bit multiplies of split 30-bit
+# operands on the vector units, 64 products of 8-bit digits on the matrix cores
+# (a multiplication and an addition each; the windows' zero padding is not counted).
 MUL32_PER_MAC = 4
+INT8_PER_MAC = 128
+
+
+def mul32_per_butterfly(ctx):
+    return MUL32_PER_BUTTERFLY[all((1 << 60) - q <= 1 << 26 for q in ctx.primes)]
+
+
 # Schedule choices measured on MI355X, reused so that the benchmark and its
 # rocprofv3 summaries run the same kernels.
 DEFAULT_TUNE_CACHE = os.path.join(ROOT, "paper_2403_11166_amd", "autotune_gfx950.txt")
@@ -189,17 +201,19 @@ def exact_mod_t(layer, op, a, b, t):
 
 # ------------------------------------------------------------- work model
 
-def kernel_work(sizes_list):
-    """Algorithmic HBM bytes and 32-bit multiplies per kernel kind over one step.
+def kernel_work(entries):
+    """Algorithmic HBM bytes and operations per kernel kind over one step, for
+    (context, layer, plan, sizes, products) entries.
 
     bytes: every polynomial the kernel must read and write once (8-byte
-    residues); multiplies: MUL32_PER_BUTTERFLY per butterfly ((N/2) log2 N per
-    limb-polynomial) and MUL32_PER_MAC per multiply-accumulate (one per
-    product, component, limb and slot).  The flood's Philox and reductions are
-    not counted (0).
+    residues); operations: 32-bit multiplies, mul32_per_butterfly per butterfly
+    ((N/2) log2 N per limb-polynomial) and MUL32_PER_MAC per multiply-accumulate
+    (one per product, component, limb and slot), or INT8_PER_MAC int8 operations
+    for one on the matrix cores.  The flood's Philox and reductions are not
+    counted (0).
     """
     work = {}
-    for ctx_, sz, ops in sizes_list:
+    for ctx_, layer_, plan_, sz, ops in entries:
         n, L = ctx_.n, ctx_.L
         lg = n.bit_length() - 1
         poly = L * n * 8
@@ -215,7 +229,7 @@ def kernel_work(sizes_list):
             else:
                 n_ct_in, n_pt = sz.n_ct[2] + sz.n_ct[3], sz.n_pt[2]
             add = lambda k, b, o: work.__setitem__(k, (work.get(k, (0, 0))[0] + b, work.get(k, (0, 0))[1] + o))  # noqa
-            b10 = MUL32_PER_BUTTERFLY * bfly
+            b10 = mul32_per_butterfly(ctx_) * bfly
             # one launch holds a product's forward transforms: plaintexts, masks and,
             # for the forward and input-gradient products, the model owner's share,
             # added to component 0 of the input ciphertexts, which is read and
@@ -223,14 +237,16 @@ def kernel_work(sizes_list):
             # multiply-accumulate reads the rest in place)
             n_share = n_ct_in if op != "dw" else 0
             add("ntt_ct" if n_share else "ntt_pt", (2 * n_share + n_pt + n_out) * poly, (n_share + n_pt + n_out) * b10)
-            add("mac", (2 * n_ct_in + n_pt + n_out + 2 * n_out) * poly,
-                MUL32_PER_MAC * sz.n_products[opi] * 2 * L * n)
+            matrix = ctx_.on_matrix_cores(layer_, plan_, op)
+            add("mac_matrix" if matrix else "mac", (2 * n_ct_in + n_pt + n_out + 2 * n_out) * poly,
+                (INT8_PER_MAC if matrix else MUL32_PER_MAC) * sz.n_products[opi] * 2 * L * n)
             add("intt_out", 2 * n_out * 2 * poly, 2 * n_out * b10)
             add("flood_mask", 2 * n_out * 2 * poly, 0)
     # the batched step's phase launches cover the same work
     get = lambda k: work.get(k, (0, 0))  # noqa: E731
     work["step_ntt"] = tuple(get("ntt_ct")[i] + get("ntt_pt")[i] for i in range(2))
     work["step_mac"] = get("mac")
+    work["step_mac_matrix"] = get("mac_matrix")
     work["step_intt"] = get("intt_out")
     work["step_flood"] = get("flood_mask")
     return work
@@ -308,13 +324,12 @@ def pencil_plus_bench(e, m, he_step_ms, torch):
             "dw01": exact_mod_t(L_, "dw", d["x1"], d["dy0"], t), "dw10": exact_mod_t(L_, "dw", d["x0"], d["dy1"], t)}
     exact = all(torch.equal(torch.remainder(res[kd][0] + res[kd][1], t), want[kd]) for kd in ops)
     # the online phase's dense part, one Z_t correlation per operator timed alone:
-    # output entries x contraction length multiply-adds, 4 32-bit multiplies each
+    # output entries x contraction length multiply-adds
     macs = L_.batch * L_.c_out * L_.h_out * L_.w_out * L_.c_in * L_.kh * L_.kw
     corr = {}
     for kind, (u, v) in ops.items():
         ms = timed_reps(lambda: GP.apply(ctx, L_, kind, u, v))
-        corr[kind] = {"ms": round(ms, 4), "mul32_Tps": round(4 * macs / (ms / 1e3) / 1e12, 3),
-                      "frac": round(4 * macs / (ms / 1e3) / 1e12 / MUL32_PEAK_TOPS, 4)}
+        corr[kind] = {"ms": round(ms, 4), "macs_Tps": round(macs / (ms / 1e3) / 1e12, 3)}
     return {"m": m, "layer": f"{L_.kind} {L_.c_in}->{L_.c_out} {L_.h}x{L_.w} b{L_.batch}",
             "prep": {"products": int(prep_products), "wall_ms": round(prep_ms, 2),
                      "products_per_s": round(prep_products / (prep_ms / 1e3), 1),
@@ -324,8 +339,7 @@ def pencil_plus_bench(e, m, he_step_ms, torch):
                        "eager_ms_per_step": round(eager_ms, 4), "operators": list(ops),
                        "he_step_ms": round(he_step_ms, 4), "speedup_vs_he_step": round(he_step_ms / online_ms, 2),
                        "bit_exact": bool(exact), "graph_replays_match_eager": bool(replay_same)},
-            "zt_correlation": {"macs_per_call": int(macs), "calls_per_step": 8, "per_operator": corr,
-                               "bound": "alu", "peak_mul32_Tps": MUL32_PEAK_TOPS}}
+            "zt_correlation": {"macs_per_call": int(macs), "calls_per_step": 8, "per_operator": corr}}
 
 
 # ------------------------------------------------------------- cpu baseline
@@ -580,7 +594,7 @@ def main():
             bit_exact &= bool(ok)
 
     # ------------------------------------------------------ roofline
-    work = kernel_work([(e["ctx"], e["sz"], cfg.ops) for e in layers])
+    work = kernel_work([(e["ctx"], e["layer"], e["plan"], e["sz"], cfg.ops) for e in layers])
     per_step = {k: (stats[k][0] / args.steps, stats[k][1] / args.steps) for k in stats if stats[k][0]}
     dom = max(per_step, key=lambda k: per_step[k][1])
     launches, ms = per_step[dom]
@@ -589,16 +603,20 @@ def main():
     avg_ms = ms / launches
     gbs = bytes_step / launches / (avg_ms / 1e3) / 1e9
     tops = ops_step / launches / (avg_ms / 1e3) / 1e12
+    on_matrix = dom.endswith("mac_matrix")
+    peak = INT8_PEAK_TOPS if on_matrix else MUL32_PEAK_TOPS
     roof = {"kernel": dom, "launches_per_step": launches, "avg_launch_ms": round(avg_ms, 5),
-            "bound": "alu", "achieved": round(tops, 3), "peak": round(MUL32_PEAK_TOPS, 3),
-            "unit": "T int32-multiply/s", "frac": round(tops / MUL32_PEAK_TOPS, 4),
+            "bound": "mfma" if on_matrix else "alu", "achieved": round(tops, 3), "peak": round(peak, 3),
+            "unit": "T int8-op/s" if on_matrix else "T int32-multiply/s", "frac": round(tops / peak, 4),
             "traffic": recorded_traffic(dom, cfg.name),
-            "work_per_launch": {"mul32": int(ops_step / launches), "algo_bytes": int(bytes_step / launches)},
+            "work_per_launch": {"int8_ops" if on_matrix else "mul32": int(ops_step / launches),
+                                "algo_bytes": int(bytes_step / launches)},
             "hbm": {"achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": round(gbs / HBM_PEAK_GBS, 4)}}
     breakdown = {k: {"launches": v[0], "ms": round(v[1], 4),
                      "algo_GBps": round(work.get(k, (0, 0))[0] / (v[1] / 1e3) / 1e9, 1) if v[1] else None,
-                     "mul32_Tps": round(work.get(k, (0, 0))[1] / (v[1] / 1e3) / 1e12, 3) if v[1] else None}
+                     ("int8_Tops" if k.endswith("mac_matrix") else "mul32_Tps"):
+                         round(work.get(k, (0, 0))[1] / (v[1] / 1e3) / 1e12, 3) if v[1] else None}
                  for k, v in sorted(per_step.items(), key=lambda kv: -kv[1][1])}
 
     # ------------------------------------------------------ NTT throughput
@@ -626,7 +644,7 @@ def main():
     for name, inv in (("forward", False), ("inverse", True)):
         ms = ntt_ms(inv)
         gbs = 16 * c0.n * npoly / (ms / 1e3) / 1e9
-        mul = MUL32_PER_BUTTERFLY * npoly * (c0.n // 2) * lg / (ms / 1e3) / 1e12
+        mul = mul32_per_butterfly(c0) * npoly * (c0.n // 2) * lg / (ms / 1e3) / 1e12
         ntt_rec[name] = {"ms": round(ms, 4), "GBps": round(gbs, 1), "hbm_frac": round(gbs / HBM_PEAK_GBS, 4),
                          "mul32_Tps": round(mul, 3), "mul32_frac": round(mul / MUL32_PEAK_TOPS, 4)}
     del polys
@@ -662,7 +680,7 @@ def main():
         # decryption transforms c1 forward and the phase back (2 L) and reads both
         # components.  Both are bound by the transforms' 32-bit multiplies.
         n_, lg_ = c.n, c.n.bit_length() - 1
-        bfly_ = MUL32_PER_BUTTERFLY * (n_ // 2) * lg_
+        bfly_ = mul32_per_butterfly(c) * (n_ // 2) * lg_
         ct_bytes = 2 * c.L * n_ * 8
 
         def ends_roof(count, ms, transforms):

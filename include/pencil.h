@@ -241,7 +241,8 @@ pencil_status pencil_linear_bwd(pencil_ctx* ctx, const pencil_layer* layer, cons
  * returns; BFV decryption of Sec. II.B).  Decrypt the n_out[op] output
  * ciphertexts of product `op` (m = round(t [c0 + c1 s]_q / q) mod t, exact
  * CRT) and gather the output slots (App. A's output positions) into share
- * (shaped like Y, dX or W).  ws: ws_dec_bytes.  EINVAL for a bad op, layer,
+ * (shaped like Y, dX or W).  Residues below 15 q_l are taken as they are, so
+ * word-wise sums of ciphertexts need no reduction.  ws: ws_dec_bytes.  EINVAL for a bad op, layer,
  * plan or pointer. */
 pencil_status pencil_decrypt(pencil_ctx* ctx, const pencil_layer* layer, const pencil_plan* plan, int op,
                              const uint64_t* ct, int64_t* share, void* ws, void* stream);
@@ -366,7 +367,9 @@ pencil_status pencil_autotune(pencil_ctx* ctx, const pencil_layer* layer, pencil
                               const char* cache_path);
 
 /* Negacyclic NTT of `count` polynomials laid out [count][L][N] (limb l of each
- * polynomial mod q_l), in place.  The transform domain is this library's
+ * polynomial mod q_l), in place.  Residues in: below 16 q_l forward, below 4 q_l
+ * inverse (with all limbs within 2^26 below 2^60, any 64-bit word forward); out:
+ * below q_l.  The transform domain is this library's
  * internal order: entry i of the forward transform holds the evaluation at
  * psi^(2 rev(i) + 1), rev = bit reversal of log2 N bits (Sec. V). */
 pencil_status pencil_ntt_forward(pencil_ctx* ctx, uint64_t* polys, int64_t count, void* stream);

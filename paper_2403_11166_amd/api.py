@@ -182,6 +182,17 @@ class Context:
         self._check(self.lib.pencil_ctx_info(self.h, ctypes.byref(info)))
         return info.ntt_loge
 
+    def on_matrix_cores(self, layer, plan, op):
+        """Whether the product's multiply-accumulate runs on the matrix cores (else on the vector units)."""
+        p, out = A.Params(), ctypes.c_int()
+        p.log2_n, p.num_limbs, p.t, p.seed = self.n.bit_length() - 1, self.L, self.t, self.seed
+        for i, q in enumerate(self.primes):
+            p.primes[i] = q
+        self._check(self.lib.pencil_product_kernel(ctypes.byref(p), ctypes.byref(layer_struct(layer)),
+                                                   ctypes.byref(plan_struct(plan)), OPS.get(op, op),
+                                                   ctypes.byref(out)))
+        return bool(out.value)
+
     def layout(self, layer, plan):
         s = A.Sizes()
         self._check(self.lib.pencil_layout(self.h, ctypes.byref(layer_struct(layer)),

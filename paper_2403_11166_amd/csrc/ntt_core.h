@@ -8,7 +8,7 @@ namespace pencil {
 
 // ----------------------------------------------------------------- NTT core
 // One workgroup transforms one limb-polynomial held in LDS.  N/E threads each
-// keep E residues in registers (E = 16, or 32 at N = 16384) and run several
+// keep E residues in registers (E = 16, or 32 if tuned so) and run several
 // butterfly stages per LDS round trip; the log2 N stages are split into
 // ceil(log2 N / log2 E) passes of near-equal size.  LDS rows are padded by one
 // word every 32 so that strided passes spread over the banks.
@@ -259,22 +259,22 @@ __device__ __forceinline__ void fwd_pass(uint64_t* a, In in, const PENCIL_GLOBAL
   }
   if (work) {
 #pragma unroll
-  for (int s = 0; s < S; ++s) {
-    const int h = 1 << (S - 1 - s);
+    for (int s = 0; s < S; ++s) {
+      const int h = 1 << (S - 1 - s);
 #pragma unroll
-    for (int r = 0; r < G; ++r) {
-      const int blk = (r * T + tid) >> LT;
+      for (int r = 0; r < G; ++r) {
+        const int blk = (r * T + tid) >> LT;
 #pragma unroll
-      for (int j = 0; j < (1 << s); ++j) {
-        const TW w = twiddle_at<S0, (SCALAR && LT >= 6)>(tw, (1 << s) + j, blk);
+        for (int j = 0; j < (1 << s); ++j) {
+          const TW w = twiddle_at<S0, (SCALAR && LT >= 6)>(tw, (1 << s) + j, blk);
 #pragma unroll
-        for (int k = j << (S - s); k < ((j + 1) << (S - s)); ++k) {
-          if (k & h) continue;
-          ct_bfly(v[r * K + k], v[r * K + k + h], w, bk, S0 + s);
+          for (int k = j << (S - s); k < ((j + 1) << (S - s)); ++k) {
+            if (k & h) continue;
+            ct_bfly(v[r * K + k], v[r * K + k + h], w, bk, S0 + s);
+          }
         }
       }
     }
-  }
   }
 #pragma unroll
   for (int r = 0; r < G; ++r) {
@@ -420,7 +420,7 @@ __device__ __forceinline__ void do_ntt_plain(uint64_t* lds, uint64_t* data, int 
   const PENCIL_GLOBAL uint64_t* g1 = gview(data + p * n);
   auto src = [g1](int i) { return g1[i]; };
   if (!inverse) {
-    // any representative below 2^64 (the plain butterflies' first stage takes it as it is)
+    // F60: any 64-bit representative, folded here; plain butterflies take one below 16 q as it is
     auto red = [&](int i) {
       if constexpr (F60) return fold60(g1[i], bfly_consts<true>(lc.q));
       else return g1[i];

@@ -263,7 +263,6 @@ struct Relayout {
 hipError_t launch_stride_relayout(const Relayout& R, const int64_t* in, int64_t* out, hipStream_t s);
 hipError_t launch_zt_corr(const int64_t* a, const int64_t* k, int64_t* out, const Geo& G, const View& AV,
                           const View& KV, const View& OV, const Consts& C, hipStream_t s);
-// width: ntt_loge, plus 8 for contexts with fold60
 // The lane-split and matrix-core Z_t correlations advance a contraction index
 // (k, dy, dx) by the mixed-radix digits of their stride.
 struct DotStep {
@@ -293,6 +292,7 @@ inline int64_t zt_matrix_splits(int64_t tiles, int64_t ctot, bool contiguous_col
 }
 hipError_t launch_zt_matrix(const int64_t* a, const int64_t* k, int64_t* out, const Geo& G, const View& AV,
                             const View& KV, const View& OV, const Consts& C, bool win, hipStream_t s);
+// width: ntt_loge, plus 8 for contexts with fold60
 hipError_t launch_step_ntt(int log2n, int width, bool inverse, const StepPhase& P, int64_t blocks, hipStream_t s);
 hipError_t launch_step_mac(const StepPhase& P, int64_t blocks, int kind, hipStream_t s);
 hipError_t launch_step_mac_matrix(const StepPhase& P, int64_t blocks, hipStream_t s);
