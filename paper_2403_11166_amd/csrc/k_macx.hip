@@ -33,8 +33,8 @@ namespace pencil {
 // staged components already in digits: a workgroup reads them from one
 // contiguous range.  Ciphertexts in the caller's buffers are a 128-byte run per
 // tile.  With both sides so (32 rows at strides of tens of MiB) the CU's
-// first-level address translations missed on every row of every block (3.6 times
-// the misses measured here).
+// first-level address translations missed several times as often; they miss on 0.5
+// % of the requests here.
 //
 // What bounds it: the operand loads.  The products of a training step of three
 // conv layers (64, 128 and 256 channels, batch 64, N = 16384, L = 4) take 9.3 ms

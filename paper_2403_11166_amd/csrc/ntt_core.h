@@ -42,8 +42,9 @@ constexpr int ntt_threads(int logn, int loge) { return (1 << logn) >> loge; }
 constexpr int ntt_min_waves(int logn, int loge) { return ntt_threads(logn, loge) > 512 || loge < 5 ? 4 : 2; }
 #define PENCIL_NTT_BOUNDS(LOGN, LOGE) __launch_bounds__(ntt_threads(LOGN, LOGE), ntt_min_waves(LOGN, LOGE))
 
-// What bounds the transforms: vector instruction issue (about 80 % of the cycles
-// of the forward launch at N = 16384), then, for the inverse, the loads and stores
+// What bounds the transforms: vector instruction issue (68 % of the SIMD cycles of
+// the forward launch at N = 16384 with four cycles an instruction, more by the costs
+// below; 52 % of the inverse's), then, for the inverse, the loads and stores
 // that nothing overlaps at one workgroup per CU.  Issue costs measured here, in
 // cycles per wave: v_and, v_add 2.5; v_alignbit, v_mul_hi, v_lshl_or 4.4-4.6;
 // 64-bit shifts and adds 5; v_mad_u64_u32 5.3.  Forward launch of three conv layers
@@ -210,8 +211,8 @@ __device__ __forceinline__ uint64_t reduce_16q(uint64_t x, uint64_t q, const Bfl
 // (e << B0) + blk, so that the lanes of a wave, which take consecutive blocks,
 // read consecutive entries.  (In the tables' natural order a thread's entries
 // are adjacent instead: each 16-byte load then touched 64 cache lines and the
-// L1, which 16 waves overran, fetched every line several times: 1.15 MB per
-// polynomial of 128 KB.)  With blocks of 64 or more groups a whole wave uses the
+// L1, which 16 waves overran, fetched every line several times: an inverse
+// transform of 128 KB, N = 16384, read 1.15 MB from the L2, and 0.79 MB now.)  With blocks of 64 or more groups a whole wave uses the
 // same entries, which SCALAR passes read through the scalar cache.  All do but the
 // encryption's with plain moduli (k_encrypt), N = 4096, L = 2, 50-bit moduli, scalar
 // against vector loads: 30 ciphertexts 22.7 and 21.8 us, 1024 189 and 186 us, but the
