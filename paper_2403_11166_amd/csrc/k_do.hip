@@ -61,16 +61,15 @@ __global__ void PENCIL_NTT_BOUNDS(LOGN, LOGE) k_phase(const uint64_t* ct, uint64
   const LimbConst& lc = C.limb[l];
   const uint64_t* c0 = ct + ((j * 2 + 0) * L + l) * n;
   // residues as the caller has them, sums of ciphertexts unreduced: any
-  // representative for the F60 butterflies, below 16 q for the others
-  const uint64_t* c1 = ct + ((j * 2 + 1) * L + l) * n;
+  // representative for the F60 butterflies, below 16 q for the others; read by the
+  // first pass itself
+  const PENCIL_GLOBAL uint64_t* c1 = gview(ct + ((j * 2 + 1) * L + l) * n);
   if constexpr (F60) {
     const BflyK<true> bk = bfly_consts<true>(lc.q);
-    for (int i = threadIdx.x; i < n; i += blockDim.x) lds[lpad(i)] = fold60(c1[i], bk);
+    ntt_fwd_in<LOGN, LOGE, F60>(lds, [&](int i) { return fold60(c1[i], bk); }, fw_table<LOGN, LOGE>(T, C, l), lc.q);
   } else {
-    for (int i = threadIdx.x; i < n; i += blockDim.x) lds[lpad(i)] = c1[i];
+    ntt_fwd_in<LOGN, LOGE, F60>(lds, [c1](int i) { return c1[i]; }, fw_table<LOGN, LOGE>(T, C, l), lc.q);
   }
-  __syncthreads();
-  ntt_fwd<LOGN, LOGE, F60>(lds, fw_table<LOGN, LOGE>(T, C, l), lc.q);
   const uint64_t* sv = s_ntt + (int64_t)l * n;
   const uint64_t* ss = s_sh + (int64_t)l * n;
   for (int i = threadIdx.x; i < n; i += blockDim.x) lds[lpad(i)] = mul_shoup(lds[lpad(i)], sv[i], ss[i], lc.q);
