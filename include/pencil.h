@@ -361,8 +361,8 @@ pencil_status pencil_stride_relayout(pencil_ctx* ctx, const pencil_layer* stride
  * and product; hits are applied without measuring, new choices are appended.
  * Synchronous; allocates and frees its own scratch buffers.  Tune a context
  * before creating steps on it: a step keeps the plans it was created with, and
- * the NTT width in force at its bind (right at any width; later ones may be
- * faster). */
+ * the NTT width in force at its bind.  Results are right at any width, so one
+ * changed while other threads call on the context does no harm. */
 pencil_status pencil_autotune(pencil_ctx* ctx, const pencil_layer* layer, pencil_plan* plan /* host, in/out */,
                               const char* cache_path);
 

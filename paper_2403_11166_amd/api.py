@@ -167,8 +167,9 @@ class Context:
         return p
 
     def autotune(self, layer, plan, cache_path=None):
-        """Measure the NTT width, the planner's best partitions and the nine multiply-accumulate
-        schedules on this GPU and return the tuned plan (tune before encrypting with it)."""
+        """Measure the NTT width, the planner's best partitions and, for products on the vector units,
+        the nine multiply-accumulate schedules on this GPU and return the tuned plan (tune before
+        encrypting with it; the width is the context's, and a Step takes the one in force at its bind)."""
         p = plan_struct(plan)
         q = A.Plan()
         ctypes.pointer(q)[0] = p

@@ -704,8 +704,9 @@ static pencil_status get_geo(pencil_ctx* ctx, const pencil_layer* L, const penci
 // Work model, in units of one pointwise product-accumulate of one residue.
 // An NTT of one limb-polynomial costs (N/2) log2 N butterflies of ~1.4 units
 // each, a product 2 components per limb; both weights are calibrated on
-// MI355X step-kernel times (N = 8192: ~88 ns per limb transform, ~19 ns per
-// limb product).  Input ciphertexts arrive in the NTT domain, split, and are
+// MI355X step-kernel times of Shoup butterflies and the vector multiply-accumulate
+// (N = 8192: ~88 ns per limb transform, ~19 ns per limb product).  They stay as
+// they are: a plan fixes the ciphertext layout, and both parties' plans must agree.  Input ciphertexts arrive in the NTT domain, split, and are
 // read in place: the MO transforms only its share for the fwd and dx operands
 // and stages component 0 with it added (the copy costing ~0.36 of a
 // transform).
